@@ -44,7 +44,7 @@ _MODELS = {
 }
 _EPS, _THETA = 1e-6, 1e6
 _PAGE = 64
-_CHUNK = 16384      # prefill chunk, the benchmark's
+_CHUNK = 16384      # prefill chunk, the benchmark's (the engine's limit, whatever a case admits)
 _ROOM = 4096        # decode steps a row has ahead of it
 
 
@@ -168,8 +168,8 @@ def prepare(case, seed):
     st.sample_seed = int(seed) & 0xFFFF
     st.temperature = 0.0 if s.dtype == "f32" else 1.0
     pages = sum(-(-(n + room - 1) // _PAGE) for n in lens)
-    st.engine = rollpack.Engine(s, w, max_seqs=rows, max_prefill_tokens=max(64, min(_CHUNK, sum(lens))),
-                                max_context=max(lens) + room, kv_pages=pages)
+    st.engine = rollpack.Engine(s, w, max_seqs=rows, max_prefill_tokens=_CHUNK, max_context=max(lens) + room,
+                                kv_pages=pages)
     st.left = 0
     if case["kind"] == "decode":
         _admit(st)
