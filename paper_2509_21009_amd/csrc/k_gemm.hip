@@ -23,13 +23,14 @@
 //    through LDS; blockIdx.y splits K further and writes fp32 partials that
 //    the consumer kernel sums.
 //  * k_gemm_tiled (M > 64: prefill and large decode batches): 128- or
-//    256-row x 128- or 256-row block tiles, 8 waves of 32x32x16 MFMAs, tiles
-//    loaded from global memory straight into a 3-stage swizzled LDS ring.
+//    256-row x 128- or 256-row block tiles of 32x32x16 MFMAs, half tiles
+//    copied from global memory straight into a swizzled LDS ring.
 //  * k_gemm_f32: fp32 FMA tiles for the fp32 model (no reduced precision).
 //
 // The SiLU epilogue pairs gate row i with up row i in one thread and writes
 // silu(gate) * up once, rounded to the storage type.
 #include <algorithm>
+#include <type_traits>
 
 #include "device_common.hpp"
 #include "kernels.hpp"
@@ -51,6 +52,16 @@ __device__ __forceinline__ const T* seg_row(const WSeg& W, int n, int K) {
 }
 
 __device__ __forceinline__ float silu(float z) { return z / (1.0f + expf(-z)); }
+// The same for results that are rounded to bf16: the quotient by a Newton-refined reciprocal, since the
+// full division sequence is half of an epilogue.  A divisor past 2^126, infinity included, has the
+// reciprocal 0, which the refinement must not turn into infinity times 0.
+__device__ __forceinline__ float silu_fast(float z) {
+  const float d = 1.0f + expf(-z);
+  const float r = __builtin_amdgcn_rcpf(d);
+  return z * (r == 0.0f ? r : __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r));
+}
+// fp32 -> bf16 storage, round to nearest even (v_cvt_pk_bf16_f32).
+__device__ __forceinline__ bf16_t bf16_of(float f) { return __builtin_bit_cast(bf16_t, static_cast<__bf16>(f)); }
 
 // ---- decode-regime weight streaming ----------------------------------------
 template <int R, int MT, bool SILU>
@@ -464,58 +475,66 @@ __global__ __launch_bounds__(256) void k_gemm_deep(GemmArgs a, int units_per_spl
 
 // ---- prefill / large-batch tiled MFMA GEMM ---------------------------------
 // Block tile: BM activation rows (m, 128 or 256) x BN weight rows (n, 128 or
-// 256), K step 32, eight waves as 2 (m) x 4 (n) for BN = 256 or 4 x 2 for
-// BN = 128, each computing BM/2 or BM/4 m x 64 n with
-// v_mfma_f32_32x32x16_bf16 (two waves per SIMD).  Activations are the MFMA
-// row operand and weights the column operand, so the 32 lanes of one
-// accumulator register hold 32 consecutive n: coalesced stores.
+// 256), K step 64, on v_mfma_f32_32x32x16_bf16.  Activations are the MFMA row
+// operand and weights the column operand, so the 32 lanes of one accumulator
+// register hold 32 consecutive n: coalesced stores.
 //
-// Tiles move from global memory straight into LDS (buffer_load_dwordx4 ...
-// lds: each wave-instruction writes 1 KB, 16 rows of 64 bytes, with no
-// register staging) through a ring of kGNST stages, issued kGNST - 1 stages
-// ahead, one barrier per K step.  The loads are inline assembly, so the
-// compiler neither tracks them nor inserts its conservative vmcnt(0) before
-// every barrier; the kernel waits with explicit vmcnt counts instead (each
-// thread issues the same NA + 2 loads per stage, and vector loads complete in
-// order).  A stage's buffer is refilled only after the barrier that follows
-// the last read of it.  The 16-byte chunk j of LDS row r holds global chunk
-// j ^ ((r >> 2) & 3): eight consecutive lanes of a fragment read then hit
-// eight distinct 16-byte bank groups.  Rows past M or N read as zeros
-// through the buffer resources (range-checked loads); a 16-row block of a
-// weight tile lies in one weight segment.  Each XCD takes a contiguous run
-// of the (split, tile) order, split-major (block ids equal mod 8), and the
-// order walks gm m tiles of one weight panel before the next panel, so the
-// 32 tiles an XCD runs at once share gm activation tiles and 32 / gm weight
-// panels in its L2.  (A run per tile with the split on blockIdx.y gave one XCD
-// every split of its tiles: at 129-256 rows the down projection's 28 panels x 9
-// splits put 36 blocks on each of seven XCDs, two rounds, and none on the
-// eighth; balanced, it runs in 49 against 93 us at 256 rows.)  gm is
-// 8 for wide products (>= 64 panels: gate/up, the LM head) and 2 for
-// narrow ones (measured: at 4k-16k rows gate/up gains 4 points of MFMA peak
-// over a single panel at a time, q/k/v, o and down 2-4).
-constexpr int kGBK = 32, kGNST = 3;
+// What bounds it is the CU's load path, not the MFMA pipes: a 256 x 256 tile
+// moves 64 KB into LDS per K step for 2048 cycles of MFMA per SIMD.  With
+// 64-byte K steps (half a cache line of every row) the loads alone took 86% of
+// the kernel's time, and a burst of a stage's copies at the barrier kept the
+// waves from issuing MFMAs until it was accepted.  Hence:
+//  * K steps of 64 elements: a copy instruction (buffer_load_dwordx4 ... lds, no
+//    register staging) takes 8 rows of one whole 128-byte line each;
+//  * the tile is two activation halves x two weight halves, and a K step has
+//    four phases, one per pair of halves.  A phase computes one pair from
+//    registers while it reads the next half's fragments and issues the copies
+//    of one half tile of a later stage, two per wave, between its MFMAs.
+//    Fragments of halves 0 are read during the step before, those of halves 1
+//    in its first two phases, so a half's LDS is free again well before its
+//    stage ends: two stages (128 KB at 256 x 256) give every copy at least one
+//    whole K step to land, with two barriers per step.
+// The copies are inline assembly, so the compiler neither tracks them nor
+// waits for all of them before a barrier; the kernel waits with explicit vmcnt
+// counts (vector loads complete in order).  Measured at 9,216 rows of the 7B
+// shapes: 1,270-1,290 TFLOP/s over the four projections (gate/up 1,280, down
+// 1,320-1,360) against 1,126 with 32-element steps, three stages and a burst
+// per stage; at 397 rows 270 against 278 us.  Measured and not kept: wave
+// priorities around the MFMAs (2% slower), and blocks that walk several tiles
+// and copy ahead across the epilogue (within 0.5% at the 7B shapes, 8% slower on
+// the 0.5B LM head).
+// The 16-byte chunk j of LDS row r holds global chunk j ^ ((r >> 1) & 7): a
+// row is 128 bytes, half of the 64 banks, so sixteen consecutive rows of a
+// fragment read hit sixteen distinct 16-byte bank groups.  Rows past M or N
+// read as zeros through the buffer resources (range-checked loads); a 16-row
+// block of a weight tile lies in one weight segment.  Each XCD takes a
+// contiguous run of the (split, tile) order, split-major (block ids equal mod
+// 8), and the order walks gm m tiles of one weight panel before the next panel,
+// so the 32 tiles an XCD runs at once share gm activation tiles and 32 / gm
+// weight panels in its L2.  gm is 8 for wide products (>= 64 panels: gate/up,
+// the LM head) and 2 for narrow ones.
+constexpr int kGBK = 64;
+// The 16-byte chunk j of LDS row r (128 bytes) holds global chunk j ^ gswz(r).
+__device__ __forceinline__ int gswz(int r) { return (r >> 1) & 7; }
 
-// Wait until at most PER * min(after, MAXJ) loads are outstanding.
-template <int PER, int J, int MAXJ>
-__device__ __forceinline__ void wait_stages_after(int after) {
-  if constexpr (J >= MAXJ) {
-    wait_vmcnt<PER * MAXJ>();
-  } else {
-    if (after == J) wait_vmcnt<PER * J>();
-    else wait_stages_after<PER, J + 1, MAXJ>(after);
-  }
-}
-__device__ __forceinline__ int gswz(int r) { return (r >> 2) & 3; }
+template <int BM, int BN>
+struct TiledCfg {
+  static constexpr int WN = BN / 64, WM = BM == 128 && BN == 128 ? 2 : 8 / WN;  // waves along n and m
+  static constexpr int WAVES = WM * WN;
+  static constexpr int MT = BM / 2 / WM / 32;          // 32-row activation tiles of a wave per half
+  static constexpr int NST = BM * BN == 256 * 256 ? 2 : BM * BN == 128 * 128 ? 2 : 3;  // LDS stages
+  static constexpr int LA = BM / 16 / WAVES, LB = BN / 16 / WAVES;  // 1 KB copies of a wave per half tile
+  static_assert(MT >= 1 && LA >= 1 && LB >= 1 && WN * 32 == BN / 2, "tile shape");
+};
 
 template <int BM, int BN, bool SILU>
-__global__ __launch_bounds__(512) void k_gemm_tiled(GemmArgs a, int kblocks_per_split, int n_mb, int n_nb, int gm) {
-  constexpr int STAGE = (BM + BN) * kGBK;       // elements per stage
-  constexpr int WMW = BN == 256 ? 2 : 4;        // waves along m (8 waves: WMW x 8 / WMW)
-  constexpr int WROWS = BM / WMW;               // activation rows per wave
-  constexpr int MT = WROWS / 32;                // 32-row activation tiles per wave
-  constexpr int NA = BM / 128, NW = BN / 128;   // 16-row blocks of activations / weights a wave loads per stage
-  static_assert(MT >= 1 && (BN == 128 || BN == 256), "tile shape");
-  __shared__ __attribute__((aligned(1024))) bf16_t smem[kGNST * STAGE];
+__global__ __launch_bounds__((64 * TiledCfg<BM, BN>::WAVES)) void k_gemm_tiled(GemmArgs a, int kblocks_per_split, int n_mb, int n_nb, int gm) {
+  using C = TiledCfg<BM, BN>;
+  constexpr int MT = C::MT, NST = C::NST, LA = C::LA, LB = C::LB, WAVES = C::WAVES;
+  constexpr int ROWB = kGBK * 2;                                   // bytes of an LDS row
+  constexpr int HA = BM / 2 * ROWB, HB = BN / 2 * ROWB, STAGE = 2 * (HA + HB);  // bytes: half tiles, a stage
+  constexpr int KS = kGBK / 16;                                    // MFMA k-steps of a stage
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[NST * STAGE];
   // Work items are (split, tile) pairs, split-major, and each XCD takes a contiguous run of
   // them (block ids equal mod 8 run on one XCD): the XCDs get equal shares of a split launch
   // (per-tile runs would hand one XCD all splits of its tiles, more blocks than its 32 CUs
@@ -532,142 +551,169 @@ __global__ __launch_bounds__(512) void k_gemm_tiled(GemmArgs a, int kblocks_per_
   const int mb = first + (t - grp * gsz) % gcur, nb = (t - grp * gsz) / gcur;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave % WMW, wn = wave / WMW;
+  const int wm = wave % C::WM, wn = wave / C::WM;
   const int l32 = lane & 31, lh = lane >> 5;
   const int K = a.K;
 
-  // Loads: wave w fills 16-row blocks w + 8 i of each tile; lane -> row lane >> 2 of the block,
-  // LDS chunk lane & 3, which holds global chunk (lane & 3) ^ gswz(row).
+  // Copies: wave w fills 8-row blocks w, w + WAVES, ... of each half tile; lane -> row lane >> 3 of
+  // the block, LDS chunk lane & 7, which holds global chunk (lane & 7) ^ gswz(row).
   const u32x4_raw ars = raw_rsrc(a.A, static_cast<uint32_t>(a.M) * static_cast<uint32_t>(a.lda) * 2u);
-  int aoff[NA], woff[NW];
-  u32x4_raw wrs[NW];
+  int aoff[2][LA], woff[2][LB];
+  u32x4_raw wrs[2][LB];
 #pragma unroll
-  for (int i = 0; i < NA; ++i) {
-    const int r = (wave + 8 * i) * 16 + (lane >> 2);
-    aoff[i] = ((mb * BM + r) * static_cast<int>(a.lda) + ((lane & 3) ^ gswz(r)) * 8) * 2;
-  }
+  for (int h = 0; h < 2; ++h) {
 #pragma unroll
-  for (int i = 0; i < NW; ++i) {
-    const int r0 = (wave + 8 * i) * 16;
-    const int r = r0 + (lane >> 2);
-    const bf16_t* wb;
-    int rel0, rows_valid;
-    if (SILU) {  // 32-row groups alternate gate / up over the same output indices
-      const int g32 = r0 >> 5;
-      wb = static_cast<const bf16_t*>(a.W.ptr[g32 & 1]);
-      rel0 = nb * (BN / 2) + (g32 >> 1) * 32 + (r0 & 31);
-      rows_valid = a.N;
-    } else {
-      const int n0 = nb * BN + r0;
-      int b = 0, sg = 0;
-      while (sg < a.W.n_seg - 1 && n0 >= b + a.W.rows[sg]) b += a.W.rows[sg++];
-      wb = static_cast<const bf16_t*>(a.W.ptr[sg]);
-      rel0 = n0 - b;
-      rows_valid = n0 < a.N ? a.W.rows[sg] : 0;
+    for (int i = 0; i < LA; ++i) {
+      const int r = (wave + WAVES * i) * 8 + (lane >> 3);
+      aoff[h][i] = ((mb * BM + h * (BM / 2) + r) * static_cast<int>(a.lda) + ((lane & 7) ^ gswz(r)) * 8) * 2;
     }
-    wrs[i] = raw_rsrc(wb, static_cast<uint32_t>(rows_valid) * static_cast<uint32_t>(K) * 2u);
-    woff[i] = ((rel0 + (lane >> 2)) * K + ((lane & 3) ^ gswz(r)) * 8) * 2;
+#pragma unroll
+    for (int i = 0; i < LB; ++i) {
+      const int r0 = (wave + WAVES * i) * 8;
+      const int r = r0 + (lane >> 3);
+      const bf16_t* wb;
+      int rel0, rows_valid;
+      if (SILU) {  // half 0: gate, half 1: up, of the same output indices
+        wb = static_cast<const bf16_t*>(a.W.ptr[h]);
+        rel0 = nb * (BN / 2) + r0;
+        rows_valid = a.N;
+      } else {
+        const int n0 = nb * BN + h * (BN / 2) + r0;
+        int b = 0, sg = 0;
+        while (sg < a.W.n_seg - 1 && n0 >= b + a.W.rows[sg]) b += a.W.rows[sg++];
+        wb = static_cast<const bf16_t*>(a.W.ptr[sg]);
+        rel0 = n0 - b;
+        rows_valid = n0 < a.N ? a.W.rows[sg] : 0;
+      }
+      wrs[h][i] = raw_rsrc(wb, static_cast<uint32_t>(rows_valid) * static_cast<uint32_t>(K) * 2u);
+      woff[h][i] = ((rel0 + (lane >> 3)) * K + ((lane & 7) ^ gswz(r)) * 8) * 2;
+    }
   }
   typedef const __attribute__((address_space(3))) char lds_char;
   const uint32_t lds0 = static_cast<uint32_t>((uintptr_t)(lds_char*)(smem));
 
-  f32x16_t acc[MT][2];
+  f32x16_t acc[2][2][MT];
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
+  for (int ah = 0; ah < 2; ++ah)
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[mt][nt][e] = 0.f;
-
-  const int kb0 = split * kblocks_per_split;
-  const int kb1 = min(kb0 + kblocks_per_split, K / kGBK);
-  auto load = [&](int st, int kb) {
-    const int ko = kb * kGBK * 2;
-    const uint32_t sa = lds0 + static_cast<uint32_t>(st * STAGE * 2), sw = sa + BM * kGBK * 2;
-#pragma unroll
-    for (int i = 0; i < NA; ++i)
-      dma16(ars, __builtin_amdgcn_readfirstlane(sa + static_cast<uint32_t>((wave + 8 * i) * 1024)), aoff[i] + ko);
-#pragma unroll
-    for (int i = 0; i < NW; ++i)
-      dma16(wrs[i], __builtin_amdgcn_readfirstlane(sw + static_cast<uint32_t>((wave + 8 * i) * 1024)), woff[i] + ko);
-  };
-  auto compute = [&](int st) {
-    const bf16_t* sA = smem + st * STAGE;
-    const bf16_t* sW = sA + BM * kGBK;
-    bf16x8_t af[2][MT], bw[2][2];
-    auto rd = [&](int buf, int ki) {
-      const int c = ki * 2 + lh;  // the lane's 16-byte chunk of this k-step
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const int r = wm * WROWS + mt * 32 + l32;
-        af[buf][mt] = *reinterpret_cast<const bf16x8_t*>(sA + r * kGBK + (c ^ gswz(r)) * 8);
-      }
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
-        const int r = wn * 64 + nt * 32 + l32;
-        bw[buf][nt] = *reinterpret_cast<const bf16x8_t*>(sW + r * kGBK + (c ^ gswz(r)) * 8);
-      }
-    };
-    // The second k-step's fragment reads are interleaved with the first k-step's MFMAs, at
-    // raised wave priority, so that the SIMD's other wave finds MFMA issue slots between them.
-    rd(0, 0);
-#pragma unroll
-    for (int ki = 0; ki < kGBK / 16; ++ki) {
-      __builtin_amdgcn_s_setprio(1);
-      if (ki + 1 < kGBK / 16) rd((ki + 1) & 1, ki + 1);
+    for (int bh = 0; bh < 2; ++bh)
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) acc[mt][nt] = mfma32x32x16(af[ki & 1][mt], bw[ki & 1][nt], acc[mt][nt]);
-      if (ki + 1 < kGBK / 16) {
-        constexpr int NRD = MT + 2, NMF = 2 * MT, NP = NRD < NMF ? NRD : NMF;
-#pragma unroll
-        for (int q = 0; q < NP; ++q) {
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // one LDS read
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
-        }
-        if constexpr (NMF > NP) __builtin_amdgcn_sched_group_barrier(0x008, NMF - NP, 0);
-        if constexpr (NRD > NP) __builtin_amdgcn_sched_group_barrier(0x100, NRD - NP, 0);
-      }
-      __builtin_amdgcn_s_setprio(0);
-    }
-  };
-#pragma unroll
-  for (int j = 0; j < kGNST - 1; ++j)
-    if (kb0 + j < kb1) load(j, kb0 + j);
-  auto step = [&](int st, int kb) {
-    // stage kb's loads were issued before those of the next kGNST - 2 stages
-    wait_stages_after<NA + NW, 0, kGNST - 2>(min(kb1 - 1 - kb, kGNST - 2));
-    __syncthreads();  // stage kb visible to all waves; stage kb - 1 no longer read
-    if (kb + kGNST - 1 < kb1) load((st + kGNST - 1) % kGNST, kb + kGNST - 1);
-    compute(st);
-  };
-  for (int kb = kb0; kb < kb1; kb += kGNST) {
-#pragma unroll
-    for (int j = 0; j < kGNST; ++j)
-      if (kb + j < kb1) step(j, kb + j);
-  }
+        for (int e = 0; e < 16; ++e) acc[ah][bh][mt][e] = 0.f;
 
-  // acc[mt][nt] register e: m = wm*WROWS + mt*32 + 8*(e/4) + 4*lh + e%4, n = wn*64 + nt*32 + l32
+  const int kb0 = split * kblocks_per_split;
+  const int kb1 = min(kb0 + kblocks_per_split, K / kGBK);
+  auto copy_a = [&](int h, int i, int st, int kb) {
+    dma16(ars, __builtin_amdgcn_readfirstlane(lds0 + static_cast<uint32_t>(st * STAGE + h * HA + (wave + WAVES * i) * 1024)),
+          aoff[h][i] + kb * ROWB);
+  };
+  auto copy_b = [&](int h, int i, int st, int kb) {
+    dma16(wrs[h][i],
+          __builtin_amdgcn_readfirstlane(lds0 + static_cast<uint32_t>(st * STAGE + 2 * HA + h * HB + (wave + WAVES * i) * 1024)),
+          woff[h][i] + kb * ROWB);
+  };
+  // Fragment reads: lane (lh, l32) takes chunk 2 ks + lh of row l32 of a 32-row group; gswz depends on l32 only.
+  const int sw = gswz(l32);
+  const uint32_t arow = (wm * MT * 32 + l32) * ROWB, brow = 2 * HA + (wn * 32 + l32) * ROWB;
+  bf16x8_t af[2][MT][KS], bw[2][KS];
+  auto rd_a = [&](int h, int ks, int st) {
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
+    for (int mt = 0; mt < MT; ++mt)
+      af[h][mt][ks] = *reinterpret_cast<const bf16x8_t*>(smem + st * STAGE + arow + (((2 * ks + lh) ^ sw) * 16) + h * HA + mt * 32 * ROWB);
+  };
+  auto rd_b = [&](int h, int ks, int st) {
+    bw[h][ks] = *reinterpret_cast<const bf16x8_t*>(smem + st * STAGE + brow + (((2 * ks + lh) ^ sw) * 16) + h * HB);
+  };
+  auto mm = [&](int ah, int bh, int ks) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int m = mb * BM + wm * WROWS + mt * 32 + 8 * (e >> 2) + 4 * lh + (e & 3);
-      if (m >= a.M) continue;
-      if (SILU) {
-        const int idx = nb * (BN / 2) + wn * 32 + l32;
-        static_cast<bf16_t*>(a.act_out)[static_cast<size_t>(m) * a.N + idx] =
-            f32_to_bf16(silu(acc[mt][0][e]) * acc[mt][1][e]);
-      } else {
-        float* out = a.part + (static_cast<size_t>(split) * a.M + m) * a.N;
+    for (int mt = 0; mt < MT; ++mt) acc[ah][bh][mt] = mfma32x32x16(af[ah][mt][ks], bw[bh][ks], acc[ah][bh][mt]);
+  };
+
+  // Copies past the last stage still issue (they read later columns, or zeros past the matrix, into
+  // stages nobody reads again), so that every wait counts the same copies.
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-          const int n = nb * BN + wn * 64 + nt * 32 + l32;
-          if (n < a.N) out[n] = acc[mt][nt][e];
-        }
-      }
+  for (int s = 0; s < NST; ++s) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int i = 0; i < LA; ++i) copy_a(h, i, s, kb0 + s);
+#pragma unroll
+      for (int i = 0; i < LB; ++i) copy_b(h, i, s, kb0 + s);
     }
+  }
+  constexpr int AHEAD = (LA + LB) * (2 * NST - 2);  // copies issued after the half tiles a barrier waits for
+  wait_vmcnt<AHEAD + LA + LB>();
+  __syncthreads();
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    rd_a(0, ks, 0);
+    rd_b(0, ks, 0);
+  }
+  int st = 0;
+  for (int kb = kb0; kb < kb1; ++kb) {
+    const int nx = st + 1 == NST ? 0 : st + 1;
+    wait_vmcnt<AHEAD>();  // halves 1 of stage kb have landed
+    __syncthreads();      // for all waves, which have halves 0 of stage kb in registers
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      if (ks < LA) copy_a(0, ks, st, kb + NST);
+      rd_b(1, ks, st);
+      mm(0, 0, ks);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      if (ks < LB) copy_b(0, ks, st, kb + NST);
+      rd_a(1, ks, st);
+      mm(0, 1, ks);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    wait_vmcnt<AHEAD>();  // halves 0 of stage kb + 1 have landed
+    __syncthreads();      // for all waves, which have halves 1 of stage kb in registers
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      if (ks < LB) copy_b(1, ks, st, kb + NST);
+      rd_a(0, ks, nx);
+      mm(1, 0, ks);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      if (ks < LA) copy_a(1, ks, st, kb + NST);
+      rd_b(0, ks, nx);
+      mm(1, 1, ks);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    st = nx;
+  }
+  wait_vmcnt<0>();  // no copy may land in this block's LDS after it ends
+
+  // acc register e of tile (ah, mt): m = ah BM/2 + (wm MT + mt) 32 + 8 (e/4) + 4 lh + e%4, n = bh BN/2 + wn 32 + l32
+  const int m0 = mb * BM + wm * MT * 32 + 4 * lh;
+  const int n0 = SILU ? nb * (BN / 2) + wn * 32 + l32 : nb * BN + wn * 32 + l32;
+  auto store = [&](auto full) {
+#pragma unroll
+    for (int ah = 0; ah < 2; ++ah)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int dm = ah * (BM / 2) + mt * 32 + 8 * (e >> 2) + (e & 3);
+          if (!full.value && m0 + dm >= a.M) continue;
+          if (SILU) {
+            bf16_t* out = static_cast<bf16_t*>(a.act_out) + static_cast<size_t>(m0) * a.N + n0;
+            out[static_cast<size_t>(dm) * a.N] = bf16_of(silu_fast(acc[ah][0][mt][e]) * acc[ah][1][mt][e]);
+          } else {
+            float* out = a.part + (static_cast<size_t>(split) * a.M + m0) * a.N + n0;
+#pragma unroll
+            for (int bh = 0; bh < 2; ++bh)
+              if (full.value || n0 + bh * (BN / 2) < a.N) out[static_cast<size_t>(dm) * a.N + bh * (BN / 2)] = acc[ah][bh][mt][e];
+          }
+        }
+  };
+  if ((mb + 1) * BM <= a.M && (SILU || (nb + 1) * BN <= a.N)) store(std::true_type{});
+  else store(std::false_type{});
 }
 
 // ---- fp32 model ------------------------------------------------------------
@@ -873,59 +919,39 @@ GemmPlan plan_deep(int M, int N, int K, bool silu, int max_splits) {
 }
 
 // k_gemm_tiled plan: the block tile (BM activation rows x BN weight rows) and
-// the K split.  A block holds one CU's LDS ring and the 8 waves of two
-// SIMD-pairs, so the time is set by rounds of 256 blocks times the K steps of
-// one block.  Decode batches (<= 512 rows) weigh every tile shape and split
-// against the fp32 partials a split adds, which at these sizes can exceed the
-// weights themselves (q/k/v at 256 rows and 14 splits: 66 MB of partials for
-// 33 MB of weights).  Prefill takes 256-row weight panels and splits K only
-// until the blocks fill one round.  The tile does not depend on max_splits,
-// so a launch with a capped split recomputes the same one.
-GemmPlan plan_tiled(int M, int N, int K, bool silu, int max_splits) {
+// the K split, each tile shape and split in [split_lo, split_hi] priced in us as
+// rounds of 256 blocks (one per CU) x (a start and an end + K steps of a block
+// x the tile's time per step), plus the fp32 partials the split writes and its
+// consumer reads.  128 x 128 tiles run two blocks per CU, alone when the last
+// round has no more than one block per CU.  Fitted to a sweep of all tile shapes
+// and splits 1-16 at 70-9,216 rows of the 7B, 0.5B and 32B projections: the
+// plans are 1.0% from the fastest in the geometric mean and at most 8%.
+GemmPlan plan_tiled(int M, int N, int K, bool silu, int split_lo, int split_hi) {
   const int KB = K / kGBK;
   GemmPlan best{kKTiled, 1};
   double best_cost = 1e300;
-  if (M <= 512) {
-    // Decode batches: every tile shape and split, priced as rounds of 256 blocks x K steps per
-    // block x the tile's cost per K step (256 x 256: 1, 256 x 128 and 128 x 256: 0.65,
-    // 128 x 128: 0.49, with one 256 x 256 step ~0.5 us), plus the fp32 partials the split
-    // writes and its consumer reads at 4 TB/s.  Fitted to a sweep of all tile shapes and splits
-    // 1-16 at 96-512 rows of the 7B projections (q/k/v, o, gate/up, down, LM head), the plan
-    // it picks is within 0.2% of the fastest in total.
-    for (int bn : {128, 256})
-      for (int bm : {256, 128}) {
-        const double tile = (bm == 256 && bn == 256) ? 1.0 : (bm == 128 && bn == 128) ? 0.4875 : 0.65;
-        const int n_tiles = (silu ? N / (bn / 2) : (N + bn - 1) / bn) * ((M + bm - 1) / bm);
-        const int s_max = silu ? 1 : std::min(16, std::max(1, KB / 4));
-        for (int sp = 1; sp <= s_max; ++sp) {
-          if (even_splits(KB, sp) != sp) continue;
-          const int rounds = (n_tiles * sp + 255) / 256;
-          const double cost = rounds * static_cast<double>((KB + sp - 1) / sp) * 0.5 * tile +
-                              (silu ? 0.0 : sp * static_cast<double>(M) * N * 8 / 4.0e6);
-          if (cost < best_cost) {
-            best_cost = cost;
-            best = GemmPlan{kKTiled, sp, 0, 0, bm, bn};
-          }
-        }
+  struct Tile { int bm, bn; double ends, step; };
+  for (const Tile& c : {Tile{256, 256, 1.5, 1.09}, Tile{256, 128, 5.5, 0.654}, Tile{128, 256, 5.5, 0.654},
+                        Tile{128, 128, 1.0, 0.955}}) {
+    const int n_tiles = (silu ? N / (c.bn / 2) : (N + c.bn - 1) / c.bn) * ((M + c.bm - 1) / c.bm);
+    for (int sp = split_lo; sp <= split_hi; ++sp) {
+      if (split_hi > split_lo && even_splits(KB, sp) != sp) continue;
+      const int items = n_tiles * sp, per = (KB + sp - 1) / sp;
+      double cost;
+      if (c.bm == 128 && c.bn == 128) {
+        const int rem = items % 512;
+        cost = (items / 512) * (c.ends + per * c.step);
+        if (rem) cost += c.ends + per * (rem <= 256 ? 0.556 : c.step);
+      } else {
+        cost = (items + 255) / 256 * (c.ends + per * c.step);
       }
-    best.splits = even_splits(KB, std::min(best.splits, max_splits));
-    return best;
-  }
-  // Prefill: 256-row weight panels; the block tile from rounds of 256 blocks times the K steps
-  // of one block, a BM = 128 step costing 0.71 of a BM = 256 one (measured at 4k rows).
-  const int bn = 256;
-  for (int bm : {256, 128}) {
-    const int blocks = (silu ? N / (bn / 2) : (N + bn - 1) / bn) * ((M + bm - 1) / bm);
-    int sp = silu ? 1 : std::max(1, 256 / blocks);
-    sp = even_splits(KB, std::min(sp, std::max(1, KB / 8)));
-    const int rounds = (blocks * sp + 255) / 256;
-    const double cost = static_cast<double>(rounds) * ((KB + sp - 1) / sp) * (bm == 256 ? 1.0 : 0.71);
-    if (cost < best_cost) {
-      best_cost = cost;
-      best = GemmPlan{kKTiled, sp, 0, 0, bm, bn};
+      if (!silu) cost += sp * static_cast<double>(M) * N * 8 / 4.2e6;
+      if (cost < best_cost) {
+        best_cost = cost;
+        best = GemmPlan{kKTiled, sp, 0, 0, c.bm, c.bn};
+      }
     }
   }
-  best.splits = even_splits(KB, std::min(best.splits, max_splits));
   return best;
 }
 
@@ -937,7 +963,7 @@ GemmPlan plan_tiled(int M, int N, int K, bool silu, int max_splits) {
 // projection at <= 16 rows), where launch latency dominates.
 GemmPlan plan_gemm(int bf16, int M, int N, int K, bool silu, int max_splits) {
   if (!bf16) return {kKF32, 1};
-  if (M > 64) return plan_tiled(M, N, K, silu, max_splits);
+  if (M > 64) return plan_tiled(M, N, K, silu, 1, silu ? 1 : std::max(1, std::min(std::min(16, max_splits), K / kGBK / 2)));
   const double work = static_cast<double>(N) * K * (silu ? 2 : 1);
   if (K % 64 == 0 && N % 16 == 0 && work >= (M > 16 ? 8.0e6 : 1.4e7)) return plan_deep(M, N, K, silu, max_splits);
   const int n_chunks = K / 128;
@@ -977,7 +1003,8 @@ hipError_t launch_gemm(int bf16, const GemmArgs& a, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
   const bool silu = a.epi == kEpiSiluMul;
   if (a.splits < 1 || (silu && a.splits != 1)) return hipErrorInvalidValue;
-  GemmPlan plan = plan_gemm(bf16, a.M, a.N, a.K, silu, kMaxSplitsAny);
+  GemmPlan plan{kKTiled, a.splits};  // more than 64 bf16 rows: the tile is chosen below, for the caller's split
+  if (!bf16 || a.M <= 64) plan = plan_gemm(bf16, a.M, a.N, a.K, silu, kMaxSplitsAny);
   if (a.variant == kKDeep && plan.kernel != kKDeep && a.M <= 64) plan = plan_deep(a.M, a.N, a.K, silu, kMaxSplitsAny);
   const int kernel = a.variant ? a.variant : plan.kernel;
   if (!bf16 || kernel == kKF32) {
@@ -995,8 +1022,7 @@ hipError_t launch_gemm(int bf16, const GemmArgs& a, hipStream_t s) {
       if (static_cast<int64_t>(a.W.rows[sg]) * a.K * 2 >= (int64_t{1} << 31)) return hipErrorInvalidValue;
       if (!silu && sg < a.W.n_seg - 1 && a.W.rows[sg] % 16 != 0) return hipErrorInvalidValue;
     }
-    GemmPlan tp{kKTiled, 1};
-    if (a.M > 64) tp = plan_tiled(a.M, a.N, a.K, silu, kMaxSplitsAny);
+    const GemmPlan tp = plan_tiled(a.M, a.N, a.K, silu, a.splits, a.splits);  // the best tile for the caller's split
     const int bm = tp.bm, bn = tp.bn;
     const int kbps = (a.K / kGBK + a.splits - 1) / a.splits;
     const int n_nb = silu ? a.N / (bn / 2) : (a.N + bn - 1) / bn;
@@ -1006,8 +1032,8 @@ hipError_t launch_gemm(int bf16, const GemmArgs& a, hipStream_t s) {
     dim3 grid(8 * per_xcd);
 #define RP_TILED(BM_, BN_)                                                                                   \
     if (bm == BM_ && bn == BN_) {                                                                            \
-      if (silu) launch_kernel((k_gemm_tiled<BM_, BN_, true>), grid, dim3(512), 0, s, a, kbps, n_mb, n_nb, gm); \
-      else launch_kernel((k_gemm_tiled<BM_, BN_, false>), grid, dim3(512), 0, s, a, kbps, n_mb, n_nb, gm); \
+      if (silu) launch_kernel((k_gemm_tiled<BM_, BN_, true>), grid, dim3((64 * TiledCfg<BM_, BN_>::WAVES)), 0, s, a, kbps, n_mb, n_nb, gm); \
+      else launch_kernel((k_gemm_tiled<BM_, BN_, false>), grid, dim3((64 * TiledCfg<BM_, BN_>::WAVES)), 0, s, a, kbps, n_mb, n_nb, gm); \
     }
     RP_TILED(128, 128) RP_TILED(128, 256) RP_TILED(256, 128) RP_TILED(256, 256)
 #undef RP_TILED

@@ -1,0 +1,55 @@
+"""Kernel edges on the GPU: tile remainders, split and dispatch boundaries, against the fp64 oracle.
+
+One-layer models of small odd widths, run through prefill and teacher-forced decode.  Bars as in the
+other parity tests: bf16 logits within 2e-2 of the oracle per position (a bf16 layer of these widths is
+0.3-1% from it), fp32 within 1e-4, ids equal wherever the oracle's top-2 margin exceeds that.
+"""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from tests.gpu_helpers import rp, teacher_forced_parity
+from workloads import ModelShape, make_weights, weights_to_numpy
+from workloads.gen import Workload
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+DEV = torch.device("cuda:0")
+SMALL = ModelShape("small", 1, 384, 6, 2, 64, 640, 1152, False, "bf16")
+
+
+def _workload(shape, plens, seed):
+    rng = np.random.default_rng(seed)
+    prompts = [rng.integers(0, shape.vocab, size=int(p)).astype(np.int32) for p in plens]
+    offs = np.concatenate([[0], np.cumsum([len(p) for p in prompts])]).astype(np.int64)
+    n = len(prompts)
+    return Workload("edges", shape, np.arange(500, 500 + n, dtype=np.int64), np.concatenate(prompts), offs,
+                    np.ones(n, np.int32), np.arange(n, dtype=np.int32), 1.0, 11)
+
+
+def _parity(shape, plens, n_new, max_prefill, tol=2e-2, check=None):
+    wd = make_weights(shape, seed=3, device=DEV)
+    w64 = weights_to_numpy(wd)
+    wl = _workload(shape, plens, len(plens) + sum(plens))
+    ctx = max(plens) + n_new
+    R = rp()
+    eng = R.Engine(shape, R.weights_for_engine(wd), max_seqs=len(plens), max_prefill_tokens=max_prefill,
+                   max_context=ctx, kv_pages=sum((p + n_new + 63) // 64 for p in plens))
+    r = teacher_forced_parity(eng, shape, w64, wl, n_new, tol, 1.0, 11, check=check)
+    eng.close()
+    assert r.max_rel_err <= tol and r.id_mismatch == 0, r
+
+
+@pytest.mark.parametrize("rows", [65, 96, 127, 128, 129, 255, 256, 257, 385, 513])
+def test_tiled_gemm_row_edges(rows):
+    """Decode batches around the tiled GEMM's 128- and 256-row tiles, prefilled from prompts of 1-3
+    tokens, so that most rows of the prefill tiles are some sequence's last and are compared too.
+    640 and 1,152 weight rows leave ragged panels, K = 384 and 640 six and ten K steps.  The engine
+    of every second case holds one split's partials only, which caps the K splits of the prefill."""
+    plens = [1 + i % 3 for i in range(rows)]
+    _parity(SMALL, plens, 2, max_prefill=sum(plens) if rows % 2 else 4096)
