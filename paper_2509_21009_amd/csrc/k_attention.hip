@@ -585,38 +585,88 @@ __global__ __launch_bounds__(64 * kPrefillWaves, 2) void k_attn_prefill_lds(Attn
 }
 
 
-// fp32 model: one wave per (row, query head), one key at a time.
-__global__ __launch_bounds__(64) void k_attn_f32(AttnArgs a) {
-  const int i = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
-  const int HD = a.hd;
-  const int G = a.n_q / a.n_kv, kh = h / G;
+// fp32 model: one block of 4 waves per (row, query head); wave w takes pages w, w + 4, ... of
+// the row's context.  Per page, lane t forms the score of token t (its K row, 16 bytes at a
+// time, the query broadcast from LDS), the wave runs one online-softmax step, and lane d sums
+// dimension d of P V over the page (V pages hold 32 consecutive tokens per dimension).  The
+// waves' maxima, sums and outputs are combined through LDS at the end.  One key at a time per
+// wave, a dependent page-table read and a wave reduction for each, took 22 us at 40 keys.
+template <int HD>
+__global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
+  constexpr int NW = 4, DPL = HD / 64;
+  __shared__ __attribute__((aligned(16))) float sq[HD];
+  __shared__ __attribute__((aligned(16))) float sp[NW][kPageTokens];
+  __shared__ float so[NW][HD], sml[NW][2];
+  const int i = blockIdx.x, h = blockIdx.y;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int kh = h / (a.n_q / a.n_kv);
   const int slot = a.tok_slot[i], pos = a.tok_pos[i];
-  const float* q = static_cast<const float*>(a.q) + (static_cast<size_t>(i) * a.n_q + h) * HD;
-  const float* kpool = static_cast<const float*>(a.k_pool);
-  const float* vpool = static_cast<const float*>(a.v_pool);
   const int* pt = a.page_table + static_cast<size_t>(slot) * a.pt_stride;
-  float qv[2] = {lane < HD ? q[lane] : 0.f, lane + 64 < HD ? q[lane + 64] : 0.f};
-  float acc[2] = {0.f, 0.f};
-  float m = -INFINITY, l = 0.f;
-  for (int t = 0; t <= pos; ++t) {
-    const size_t pb = (static_cast<size_t>(pt[t / kPageTokens]) * a.n_kv + kh) * kPageTokens * HD;
-    const int off = t % kPageTokens;
-    const float* k = kpool + pb + static_cast<size_t>(off) * HD;
-    float part = (lane < HD ? qv[0] * k[lane] : 0.f) + (lane + 64 < HD ? qv[1] * k[lane + 64] : 0.f);
-    const float s = wave_sum(part) * a.scale;
-    const float m_new = fmaxf(m, s);
+  if (threadIdx.x < HD) sq[threadIdx.x] = static_cast<const float*>(a.q)[(static_cast<size_t>(i) * a.n_q + h) * HD + threadIdx.x];
+  __syncthreads();
+  float acc[DPL], m = -INFINITY, l = 0.f;
+#pragma unroll
+  for (int k = 0; k < DPL; ++k) acc[k] = 0.f;
+  const int npages = pos / kPageTokens + 1;
+  for (int p = wave; p < npages; p += NW) {
+    const size_t pb = (static_cast<size_t>(pt[p]) * a.n_kv + kh) * kPageTokens * HD;
+    const int left = min(pos + 1 - p * kPageTokens, kPageTokens);  // tokens of the page the row attends to (>= 1)
+    // V rows of this lane's dimensions do not depend on the scores: their loads run beside those of K
+    const f32x4_t* vr = reinterpret_cast<const f32x4_t*>(static_cast<const float*>(a.v_pool) + pb);
+    const f32x4_t* kr = reinterpret_cast<const f32x4_t*>(static_cast<const float*>(a.k_pool) + pb + static_cast<size_t>(min(lane, left - 1)) * HD);
+    const f32x4_t* q4 = reinterpret_cast<const f32x4_t*>(sq);
+    f32x4_t d4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < HD / 4; ++c) {
+      const f32x4_t kv = kr[c], qv = q4[c];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) d4[e] = fmaf(kv[e], qv[e], d4[e]);
+    }
+    const float s = lane < left ? ((d4[0] + d4[1]) + (d4[2] + d4[3])) * a.scale : -INFINITY;
+    const float m_new = fmaxf(m, wave_max(s));
     const float alpha = expf(m - m_new);
-    const float p = expf(s - m_new);
-    l = l * alpha + p;
+    const float pr = lane < left ? expf(s - m_new) : 0.f;
+    l = l * alpha + wave_sum(pr);
     m = m_new;
-    const float* v = vpool + pb;
-    const float* vh = v + (off >> 5) * HD * 32 + (off & 31);
-    if (lane < HD) acc[0] = acc[0] * alpha + p * vh[static_cast<size_t>(lane) * 32];
-    if (lane + 64 < HD) acc[1] = acc[1] * alpha + p * vh[static_cast<size_t>(lane + 64) * 32];
+    sp[wave][lane] = pr;  // read by this wave only
+    __builtin_amdgcn_wave_barrier();
+    const f32x4_t* p4 = reinterpret_cast<const f32x4_t*>(sp[wave]);
+#pragma unroll
+    for (int k = 0; k < DPL; ++k) {
+      f32x4_t o4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          const int t0 = hf * 32 + 4 * c;
+          if (t0 >= left) continue;  // wave-uniform; tokens past the row's position are never multiplied in
+          const f32x4_t vv = vr[(hf * HD + lane + 64 * k) * 8 + c], pv = p4[t0 / 4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o4[e] = fmaf(t0 + e < left ? vv[e] : 0.f, pv[e], o4[e]);
+        }
+      acc[k] = acc[k] * alpha + ((o4[0] + o4[1]) + (o4[2] + o4[3]));
+    }
+    __builtin_amdgcn_wave_barrier();
   }
-  float* out = static_cast<float*>(a.out) + (static_cast<size_t>(i) * a.n_q + h) * HD;
-  if (lane < HD) out[lane] = acc[0] / l;
-  if (lane + 64 < HD) out[lane + 64] = acc[1] / l;
+#pragma unroll
+  for (int k = 0; k < DPL; ++k) so[wave][lane + 64 * k] = acc[k];
+  if (lane == 0) {
+    sml[wave][0] = m;
+    sml[wave][1] = l;
+  }
+  __syncthreads();
+  if (threadIdx.x < HD) {
+    float mx = sml[0][0];  // wave 0 always has a page
+    for (int w = 1; w < NW; ++w) mx = fmaxf(mx, sml[w][0]);
+    float num = 0.f, den = 0.f;
+    for (int w = 0; w < NW; ++w) {
+      const float f = sml[w][0] == -INFINITY ? 0.f : expf(sml[w][0] - mx);
+      num += f * so[w][threadIdx.x];
+      den += f * sml[w][1];
+    }
+    static_cast<float*>(a.out)[(static_cast<size_t>(i) * a.n_q + h) * HD + threadIdx.x] = num / den;
+  }
 }
 
 }  // namespace
@@ -632,12 +682,17 @@ int attn_prefill_tokens_per_item(int bf16, int group) {
   return kPrefillWaves * kPrefillWaveGroups * prefill_group_tokens(group);
 }
 
+static hipError_t launch_attn_f32(const AttnArgs& a, hipStream_t s) {
+  if (a.n_rows <= 0) return hipSuccess;
+  if (a.hd == 128) launch_kernel(k_attn_f32<128>, dim3(a.n_rows, a.n_q), dim3(256), 0, s, a);
+  else if (a.hd == 64) launch_kernel(k_attn_f32<64>, dim3(a.n_rows, a.n_q), dim3(256), 0, s, a);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
 hipError_t launch_attn_decode(int bf16, const AttnArgs& a, hipStream_t s) {
   if (!bf16) {
-    if (a.n_rows <= 0) return hipSuccess;
-    if (a.hd > 128) return hipErrorInvalidValue;
-    launch_kernel(k_attn_f32, dim3(a.n_rows, a.n_q), dim3(64), 0, s, a);
-    return hipGetLastError();
+    return launch_attn_f32(a, s);
   }
   if (a.B <= 0 || a.total_splits <= 0) return hipSuccess;
   if (a.n_q / a.n_kv > 16 || a.tokens_per_split % kPageTokens != 0 || !a.split_desc) return hipErrorInvalidValue;
@@ -672,10 +727,7 @@ hipError_t launch_attn_merge(const AttnArgs& a, hipStream_t s) {
 
 hipError_t launch_attn_prefill(int bf16, const AttnArgs& a, hipStream_t s) {
   if (!bf16) {
-    if (a.n_rows <= 0) return hipSuccess;
-    if (a.hd > 128) return hipErrorInvalidValue;
-    launch_kernel(k_attn_f32, dim3(a.n_rows, a.n_q), dim3(64), 0, s, a);
-    return hipGetLastError();
+    return launch_attn_f32(a, s);
   }
   if (a.total_items <= 0) return hipSuccess;
   const int G = a.n_q / a.n_kv;

@@ -25,7 +25,7 @@
 //  * k_gemm_tiled (M > 64: prefill and large decode batches): 128- or
 //    256-row x 128- or 256-row block tiles of 32x32x16 MFMAs, half tiles
 //    copied from global memory straight into a swizzled LDS ring.
-//  * k_gemm_f32: fp32 FMA tiles for the fp32 model (no reduced precision).
+//  * k_gemm_f32: fp32 MFMA for the fp32 model (no reduced precision).
 //
 // The SiLU epilogue pairs gate row i with up row i in one thread and writes
 // silu(gate) * up once, rounded to the storage type.
@@ -717,71 +717,113 @@ __global__ __launch_bounds__((64 * TiledCfg<BM, BN>::WAVES)) void k_gemm_tiled(G
 }
 
 // ---- fp32 model ------------------------------------------------------------
-template <bool SILU>
+// One block per 16 weight rows (with the SiLU epilogue: 16 gate and the 16 up
+// rows of the same outputs) and up to 64 activation rows, on
+// v_mfma_f32_16x16x4_f32 (fp32 products and sums).  The small fp32 decoder's
+// products are launch- and latency-bound, so the K range is spread over the
+// block's 4 waves in interleaved 16-wide chunks, whose loads are all independent:
+// lane (g, r) reads elements 4g .. 4g + 3 of a row's chunk, and MFMA j takes the
+// j-th of them from both operands, so every product is formed once.  VEC: rows
+// are 16-byte aligned (one load per chunk); otherwise element loads.
+// 8 rows, K = 256: 3-4 us a launch against 33-64 us for one 64 x 64 tile per
+// block walking all of K (4-32 blocks, a barrier per 16 elements).
+template <int MT, bool SILU, bool VEC>
 __global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs a) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  constexpr int NW = SILU ? 2 : 1;
-  __shared__ float As[BK][BM + 1];
-  __shared__ float Ws[NW][BK][BN + 1];
-  const int tid = threadIdx.x;
-  const int tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  const float* A = static_cast<const float*>(a.A);
-  float acc[NW][4][4];
+  constexpr int R = SILU ? 2 : 1, U = 4;  // weight fragments; chunks in flight per wave
+  __shared__ __attribute__((aligned(16))) f32x4_t red[3][R * MT][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, r = lane & 15;
+  const int K = a.K, m0 = blockIdx.y * (16 * MT);
+  const float* wrow[R];
+  const float* arow[MT];
+  const int n_ld = min(static_cast<int>(blockIdx.x) * 16 + r, a.N - 1);  // rows past the end are not stored
 #pragma unroll
-  for (int w = 0; w < NW; ++w)
+  for (int t = 0; t < R; ++t)
+    wrow[t] = SILU ? static_cast<const float*>(a.W.ptr[t]) + static_cast<size_t>(n_ld) * K : seg_row<float>(a.W, n_ld, K);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+  for (int mt = 0; mt < MT; ++mt)
+    arow[mt] = static_cast<const float*>(a.A) + static_cast<size_t>(min(m0 + mt * 16 + r, a.M - 1)) * a.lda;
+  auto load4 = [&](const float* p, int k) {
+    f32x4_t v{0.f, 0.f, 0.f, 0.f};
+    if (VEC) {
+      if (k < K) v = *reinterpret_cast<const f32x4_t*>(p + k);
+    } else {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[w][i][j] = 0.f;
-
-  for (int k0 = 0; k0 < a.K; k0 += BK) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int e = tid + 256 * i;
-      const int row = e >> 4, kk = e & 15;
-      const int m = m0 + row, k = k0 + kk, n = n0 + row;
-      As[kk][row] = (m < a.M && k < a.K) ? A[static_cast<size_t>(m) * a.lda + k] : 0.f;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        float v = 0.f;
-        if (n < a.N && k < a.K) {
-          const float* wr = SILU ? static_cast<const float*>(a.W.ptr[w]) + static_cast<size_t>(n) * a.K
-                                 : seg_row<float>(a.W, n, a.K);
-          v = wr[k];
-        }
-        Ws[w][kk][row] = v;
-      }
+      for (int j = 0; j < 4; ++j)
+        if (k + j < K) v[j] = p[k + j];
     }
-    __syncthreads();
+    return v;
+  };
+  f32x4_t acc[R][MT];
 #pragma unroll
-    for (int kk = 0; kk < BK; ++kk) {
-      float av[4];
+  for (int t = 0; t < R; ++t)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = As[kk][ty * 4 + i];
+    for (int mt = 0; mt < MT; ++mt) acc[t][mt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int n_chunks = (K + 15) / 16;
+  for (int c0 = wave; c0 < n_chunks; c0 += 4 * U) {
+    f32x4_t wv[U][R], av[U][MT];
 #pragma unroll
-      for (int w = 0; w < NW; ++w)
+    for (int u = 0; u < U; ++u) {
+      const int k = (c0 + 4 * u) * 16 + 4 * g;  // chunks past the end load zeros
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const float wv = Ws[w][kk][tx * 4 + j];
+      for (int t = 0; t < R; ++t) wv[u][t] = load4(wrow[t], k);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) acc[w][i][j] = fmaf(av[i], wv, acc[w][i][j]);
-        }
+      for (int mt = 0; mt < MT; ++mt) av[u][mt] = load4(arow[mt], k);
     }
-    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int t = 0; t < R; ++t)
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt)
+            acc[t][mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[u][t][j], av[u][mt][j], acc[t][mt], 0, 0, 0);
   }
+  if (wave > 0) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty * 4 + i;
+    for (int t = 0; t < R; ++t)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) red[wave - 1][t * MT + mt][lane] = acc[t][mt];
+  }
+  __syncthreads();
+  if (wave > 0) return;
+  // lane (g, r) holds C^T[n = 16 block + 4g + e][m = m0 + mt*16 + r]
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    const int m = m0 + mt * 16 + r;
     if (m >= a.M) continue;
+    f32x4_t v[R];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
+    for (int t = 0; t < R; ++t)
+      v[t] = acc[t][mt] + red[0][t * MT + mt][lane] + red[1][t * MT + mt][lane] + red[2][t * MT + mt][lane];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int n = blockIdx.x * 16 + 4 * g + e;
       if (n >= a.N) continue;
-      if (SILU) static_cast<float*>(a.act_out)[static_cast<size_t>(m) * a.N + n] = silu(acc[0][i][j]) * acc[NW - 1][i][j];
-      else a.part[static_cast<size_t>(m) * a.N + n] = acc[0][i][j];
+      if (SILU) static_cast<float*>(a.act_out)[static_cast<size_t>(m) * a.N + n] = silu(v[0][e]) * v[R - 1][e];
+      else a.part[static_cast<size_t>(m) * a.N + n] = v[0][e];
     }
   }
+}
+
+template <int MT, bool SILU>
+void launch_f32_t(const GemmArgs& a, hipStream_t s) {
+  dim3 grid((a.N + 15) / 16, (a.M + 16 * MT - 1) / (16 * MT));
+  uintptr_t addr = reinterpret_cast<uintptr_t>(a.A);
+  for (int sg = 0; sg < a.W.n_seg; ++sg) addr |= reinterpret_cast<uintptr_t>(a.W.ptr[sg]);
+  if (addr % 16 == 0 && a.K % 4 == 0 && a.lda % 4 == 0)
+    launch_kernel((k_gemm_f32<MT, SILU, true>), grid, dim3(256), 0, s, a);
+  else
+    launch_kernel((k_gemm_f32<MT, SILU, false>), grid, dim3(256), 0, s, a);
+}
+
+template <bool SILU>
+void launch_f32(const GemmArgs& a, hipStream_t s) {
+  if (a.M <= 16) launch_f32_t<1, SILU>(a, s);
+  else if (a.M <= 32) launch_f32_t<2, SILU>(a, s);
+  else launch_f32_t<4, SILU>(a, s);
 }
 
 template <int R, int MT, bool SILU>
@@ -1009,9 +1051,8 @@ hipError_t launch_gemm(int bf16, const GemmArgs& a, hipStream_t s) {
   const int kernel = a.variant ? a.variant : plan.kernel;
   if (!bf16 || kernel == kKF32) {
     if (bf16 || a.splits != 1) return hipErrorInvalidValue;
-    dim3 grid((a.N + 63) / 64, (a.M + 63) / 64);
-    if (silu) launch_kernel(k_gemm_f32<true>, grid, dim3(256), 0, s, a);
-    else launch_kernel(k_gemm_f32<false>, grid, dim3(256), 0, s, a);
+    if (silu) launch_f32<true>(a, s);
+    else launch_f32<false>(a, s);
     return hipGetLastError();
   }
   if (kernel == kKTiled || a.M > 64) {

@@ -53,3 +53,17 @@ def test_tiled_gemm_row_edges(rows):
     of every second case holds one split's partials only, which caps the K splits of the prefill."""
     plens = [1 + i % 3 for i in range(rows)]
     _parity(SMALL, plens, 2, max_prefill=sum(plens) if rows % 2 else 4096)
+
+
+@pytest.mark.parametrize("hd,inter,vocab,plens", [
+    (64, 75, 301, [1, 7, 16]),                       # K = 75: element loads; ragged 16-row tiles
+    (128, 76, 320, [64, 65, 129] + [5] * 14),        # 17 rows: two activation tiles; page edges
+    (64, 690, 1001, [321, 260, 3] + [2] * 37),       # 40 rows, four tiles; contexts of more pages than waves
+    (128, 132, 130, [700]),                          # one row, eleven pages
+])
+def test_fp32_model_edges(hd, inter, vocab, plens):
+    """fp32 products with ragged N, K that is no multiple of 4 or 16, 1 to 64+ activation rows, and
+    attention over one to eleven pages (four waves per row share them).  fp32 sums of up to 690
+    products of either order agree to about 1e-6; the bar is the fp32 model's 1e-4."""
+    shape = ModelShape("f32", 2, 132, 6, 2, hd, inter, vocab, False, "f32")
+    _parity(shape, plens, 3, max_prefill=2048, tol=1e-4)
