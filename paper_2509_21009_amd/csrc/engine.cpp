@@ -17,6 +17,7 @@
 #include <deque>
 #include <map>
 #include <numeric>
+#include <utility>
 
 namespace rollpack {
 
@@ -553,7 +554,8 @@ void Engine::forward(int M, bool pre, int n_seq, int total_items, int total_spli
 
     RopeArgs ra{part, s_qkv, M, L.bq, L.bk, L.bv, nq, nkv, hd, m_pos_, m_slot_, pt, plan_.max_pages,
                 sp<float>(plan_.rope_cos), sp<float>(plan_.rope_sin), q, kpool, vpool};
-    launch_timed(RP_K_ROPE_APPEND, Md * nqkv_ * (4.0 + e), 0, [&] { return launch_rope_append(bf16_, ra, s); });
+    if (pre || !bf16_)  // the bf16 decode attention rotates and appends by itself
+      launch_timed(RP_K_ROPE_APPEND, Md * nqkv_ * (4.0 + e), 0, [&] { return launch_rope_append(bf16_, ra, s); });
 
     AttnArgs aa{};
     aa.q = q; aa.k_pool = kpool; aa.v_pool = vpool; aa.page_table = pt; aa.pt_stride = plan_.max_pages;
@@ -568,9 +570,10 @@ void Engine::forward(int M, bool pre, int n_seq, int total_items, int total_spli
       aa.B = M; aa.row_slot = m_slot_; aa.row_ctx = m_ctx_; aa.split_off = m_split_off_;
       aa.total_splits = total_splits; aa.tokens_per_split = tps; aa.split_desc = m_split_desc_;
       aa.max_row_splits = max_row_splits_;
+      aa.rope = ra;
       aa.part_o = sp<float>(plan_.att_o); aa.part_ml = sp<float>(plan_.att_ml);
       launch_timed(RP_K_ATTN, attn_bytes, attn_flops, [&] { return launch_attn_decode(bf16_, aa, s); });
-      if (bf16_) {
+      if (bf16_ && max_row_splits_ > 1) {
         const double pbytes = static_cast<double>(total_splits) * nkv * (nq / nkv) * (hd + 2.0) * 4;
         launch_timed(RP_K_ATTN_MERGE, pbytes + Md * nq * hd * e, 0, [&] { return launch_attn_merge(aa, s); });
       }
@@ -800,6 +803,36 @@ void Engine::prefill(int32_t n, const int64_t* ids, const int32_t* toks, const i
   }
 }
 
+// Pages of cached keys per decode attention item.  An item is a block of four waves; two blocks fit a CU,
+// which moves a page of one head (K and V, 32 KB at head_dim 128) in about 1.3 us whether it runs one
+// block or two.  The cost of a size, in us: the fullest CU's pages and the items' own ends (2.5 us each),
+// plus, when some row has more than one item, the merge (4.5 us).  Over sizes forced from 1 page to
+// whole rows at 1-330 rows of 64-12,000 tokens (7B, 0.5B and 32B layers) its choices are within 1-2% of
+// the fastest step; the optimum is flat.
+int Engine::decode_pages_per_item(int64_t total_pages, int64_t max_pages, int B) const {
+  const double page_us = cfg_.head_dim == 128 ? 1.3 : 0.65, ends_us = 2.5, merge_us = 4.5;
+  const int64_t target = decode_split_target(cfg_);  // the item capacity: total_pages / pps + B items at most
+  const int64_t least = std::max<int64_t>(1, (total_pages + target - 1) / target);
+  int64_t best = std::max(least, max_pages);
+  double best_us = 1e300;
+  for (int64_t pps = least;; pps += std::max<int64_t>(1, pps / 8)) {
+    pps = std::min(pps, std::max(least, max_pages));
+    const bool merge = pps < max_pages;
+    const double items = merge ? (static_cast<double>(total_pages) / pps + 0.5 * B) * cfg_.n_kv_heads
+                               : static_cast<double>(B) * cfg_.n_kv_heads;
+    const double one = pps * page_us + ends_us;
+    const double all = (static_cast<double>(total_pages) * cfg_.n_kv_heads * page_us + items * ends_us) / 256;
+    // up to one block per CU the longest item ends the step; past that the CUs even out to half an item
+    const double us = (items <= 256 ? one : std::max(one, all + 0.5 * one)) + (merge ? merge_us : 0.0);
+    if (us < best_us) {
+      best_us = us;
+      best = pps;
+    }
+    if (pps >= max_pages) break;
+  }
+  return static_cast<int>(best);
+}
+
 int32_t Engine::decode_step(const int32_t* forced, float* logits_out, int64_t* row_ids_out) {
   if (forced && kv_policy_ == RP_KV_ON_DEMAND)
     throw RpError(RP_ERR_INVALID_ARG, "teacher forcing needs the reserving KV policy");
@@ -819,22 +852,22 @@ int32_t Engine::decode_step(const int32_t* forced, float* logits_out, int64_t* r
   // Per-row context first: the split plan sizes the metadata.
   std::vector<int32_t>& ctx_h = ctx_scratch_;
   ctx_h.resize(B);
-  int64_t total_pages = 0;
+  int64_t total_pages = 0, max_pages = 0;  // of cached keys, which exclude the step's own token
   sum_ctx_ = 0;
   for (int i = 0; i < B; ++i) {
     const Seq& q = slots_[rows[i]];
     ctx_h[i] = q.prompt_len + q.n_gen;
-    total_pages += PagePool::pages_for(ctx_h[i], kPageTokens);
+    const int64_t p = PagePool::pages_for(ctx_h[i] - 1, kPageTokens);
+    total_pages += p;
+    max_pages = std::max(max_pages, p);
     sum_ctx_ += ctx_h[i];
   }
   int tps = 0, total_splits = 0;
   if (bf16_) {
-    const int64_t target = decode_split_target(cfg_);
-    const int64_t pps = std::max<int64_t>(1, (total_pages + target - 1) / target);
-    tps = static_cast<int>(pps * kPageTokens);
+    tps = decode_pages_per_item(total_pages, max_pages, B) * kPageTokens;
     max_row_splits_ = 0;
     for (int i = 0; i < B; ++i) {
-      const int n = (ctx_h[i] + tps - 1) / tps;
+      const int n = (ctx_h[i] - 1 + tps - 1) / tps;  // over the cached keys; the newest token rides on the last
       total_splits += n;
       max_row_splits_ = std::max(max_row_splits_, n);
     }
@@ -861,14 +894,29 @@ int32_t Engine::decode_step(const int32_t* forced, float* logits_out, int64_t* r
     gen_pos[i] = pos[i] + 1;
     gen_hist[i] = q.n_gen;
     split_off[i] = sx;
-    if (bf16_) {
-      // one descriptor per split: row (+ 2^30 when it is the row's only split), key range, slot
-      const int n = (ctx[i] + tps - 1) / tps;
-      for (int j = 0; j < n; ++j, ++sx) {
-        desc[4 * sx + 0] = i | (n == 1 ? (1 << 30) : 0);
-        desc[4 * sx + 1] = j * tps;
-        desc[4 * sx + 2] = std::min(j * tps + tps, ctx[i]);
-        desc[4 * sx + 3] = rows[i];
+    if (bf16_) sx += (pos[i] + tps - 1) / tps;
+  }
+  if (bf16_) {
+    // One descriptor per item, the longest first (by pages, counted per length), so that the last
+    // blocks to start are the short ones.
+    std::vector<int32_t>& at = item_at_;
+    const int pmax = tps / kPageTokens;
+    at.assign(static_cast<size_t>(pmax) + 2, 0);
+    for (int i = 0; i < B; ++i) {
+      const int full = (pos[i] - 1) / tps, last = pos[i] - full * tps;  // last: 1 .. tps keys
+      at[0] += full;
+      at[pmax - (last + kPageTokens - 1) / kPageTokens] += 1;
+    }
+    for (int k = 0, sum = 0; k <= pmax + 1; ++k) sum += std::exchange(at[k], sum);
+    for (int i = 0; i < B; ++i) {
+      const int n = (pos[i] + tps - 1) / tps;
+      for (int j = 0; j < n; ++j) {
+        const int end = std::min(j * tps + tps, pos[i]);
+        int32_t* d4 = desc + 4 * static_cast<size_t>(at[pmax - (end - j * tps + kPageTokens - 1) / kPageTokens]++);
+        d4[0] = i | (n == 1 ? (1 << 30) : 0) | (j + 1 == n ? (1 << 29) : 0);
+        d4[1] = j * tps;
+        d4[2] = end;
+        d4[3] = rows[i];
       }
     }
   }

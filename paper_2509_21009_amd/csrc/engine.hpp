@@ -176,6 +176,7 @@ class Engine {
   void mark(size_t k);
   double mark_ms(size_t a, size_t b);
 
+  int decode_pages_per_item(int64_t total_pages, int64_t max_pages, int B) const;
   void forward(int M, bool is_prefill, int n_seq_prefill, int total_items, int total_splits, int tps);
   int32_t* stage_meta(size_t ints);
   void upload_meta(const int32_t* host, size_t ints);
@@ -287,6 +288,7 @@ class Engine {
                 *m_item_off_ = nullptr, *m_last_row_ = nullptr, *m_gen_pos_ = nullptr,
                 *m_gen_hist_ = nullptr, *m_gen_slot_ = nullptr, *m_split_desc_ = nullptr;
   std::vector<int32_t> ctx_scratch_;  // decode_step: per-row context lengths
+  std::vector<int32_t> item_at_;      // decode_step: attention item counts by length
   int max_row_splits_ = 0;            // decode_step: most attention splits of any row
   std::vector<hipEvent_t> events_;
 

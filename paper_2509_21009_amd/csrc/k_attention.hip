@@ -1,7 +1,8 @@
 // Causal GQA attention over the paged KV cache.
 //
-// Decode: one 64-lane wave owns a work item: the G query heads of a token
-// (up to 16 query rows that share one KV head) and a range of KV tokens.  Per 32-token half page it computes
+// Decode: a block of four waves owns a work item: the G query heads of a token
+// (up to 16 query rows that share one KV head) and a range of KV tokens, whose
+// half pages its waves take in turn.  Per 32-token half page a wave computes
 // S^T = K Q^T as two 16x16 MFMA tiles, runs an online softmax in the log2
 // domain, and accumulates O^T = V^T P^T with MFMA.  Both operands are read
 // as 16-byte pieces straight from HBM, each load instruction one contiguous
@@ -10,16 +11,19 @@
 // and a V page as two 32-token halves, each transposed ([hd][32 tokens]).
 // The tokens are assigned to MFMA rows so that each lane's softmax outputs
 // are exactly the P^T operand it must supply, with no data exchange between
-// lanes.
+// lanes.  The kernel also rotates its queries and appends the step's key and
+// value, straight from the projection's partials.
 //
 // Prefill stages each K/V page in LDS once per block of query tokens
 // (k_attn_prefill_lds below); its waves run the same page step from LDS.
 //
-// Decode splits each sequence's context into chunks (one work item each, with
+// Decode splits long contexts into chunks (one work item each, with
 // a host-built descriptor) so that small batches with long contexts still
-// spread over all CUs; the half pages of an item stream through a ring of
-// register stages.  A merge kernel combines the chunk maxima, sums and
-// partial outputs.
+// spread over all CUs; a wave's half pages stream through a ring of
+// register stages.  A merge kernel combines the maxima, sums and
+// partial outputs of rows with more than one item.
+#include <type_traits>
+
 #include "device_common.hpp"
 #include "kernels.hpp"
 #include "lds_dma.hpp"
@@ -49,26 +53,46 @@ __device__ __forceinline__ bf16x8_t load_bf16x8_nt(const bf16_t* p) {
   return __builtin_bit_cast(bf16x8_t, __builtin_nontemporal_load(reinterpret_cast<const u32x4_nt*>(p)));
 }
 
+typedef __bf16 bf16x2_hw __attribute__((ext_vector_type(2)));
+typedef float f32x2_hw __attribute__((ext_vector_type(2)));
+
+// Two fp32 values to packed bf16, round to nearest even (gfx950's v_cvt_pk_bf16_f32; for the
+// finite values here the same result as f32_to_bf16).
+__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_hw{lo, hi}, bf16x2_hw));
+}
+
+// Decode attention of one work item: (row, KV head, range of cached keys), one block of 4 waves.
+// The block sums the q/k/v projection's split partials of its G query heads itself, adds the
+// bias and rotates them into LDS, while its first K/V loads are already in flight; the item with
+// the row's newest token does the same for that token's K and V, appends them to the cache and
+// attends to them from LDS.  (One wave per item with its own prologue in front of its first
+// load lost 8 us per layer against a launch of its own for rotation and append; shared by
+// four waves and behind the loads it costs less than the launch.)  Waves take the item's half
+// pages in turn and combine their softmax states in LDS, so partial outputs are a quarter of those of
+// one-wave items, and rows of similar lengths need no merge launch.  Bound by HBM at many rows: 330
+// rows of 200-1,700 tokens at the 7B layer stream 5.4 TB/s, 118 us against 148 for one-wave items with
+// rotation, append and merge launches; 256 rows at the 0.5B layer 22 against 32 us; by latency at few
+// (one row of 12k tokens: 10 + 6 us with its merge against 20).
+constexpr int kDecodeWaves = 4;
+
 template <int HD>
-__global__ __launch_bounds__(64) void k_attn_decode_bf16(AttnArgs a) {
-  constexpr int KS = HD / 32, NB = HD / 16, D = 2;
-  const int lane = threadIdx.x, g = lane >> 4, c = lane & 15;
-  const int x = blockIdx.x, kh = blockIdx.y;
-  const int4 dsc = reinterpret_cast<const int4*>(a.split_desc)[x];
-  const int b = dsc.x & 0x3fffffff;
-  const bool single = (dsc.x >> 30) & 1;
-  const int t0 = dsc.y, t1 = dsc.z, slot = dsc.w;
+__global__ __launch_bounds__(64 * kDecodeWaves, 2) void k_attn_decode_bf16(AttnArgs a) {
+  constexpr int KS = HD / 32, NB = HD / 16, D = 2, NW = kDecodeWaves, HALF = HD / 2;
+  constexpr int OLD = HD + 4;  // padded row of the waves' outputs (floats)
+  __shared__ __attribute__((aligned(16))) bf16_t sq[16 * HD], snk[HD], snv[HD];
+  __shared__ __attribute__((aligned(16))) float so[NW][16 * OLD];
+  __shared__ float sm[NW][16], sl[NW][16];
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int item = blockIdx.x / a.n_kv, kh = blockIdx.x - item * a.n_kv;
+  const int4 dsc = reinterpret_cast<const int4*>(a.split_desc)[item];
+  const int row = __builtin_amdgcn_readfirstlane(dsc.x), b = row & 0x1fffffff;
+  const bool single = (row >> 30) & 1, append = (row >> 29) & 1;
+  const int t0 = __builtin_amdgcn_readfirstlane(dsc.y), t1 = __builtin_amdgcn_readfirstlane(dsc.z);
+  const int slot = __builtin_amdgcn_readfirstlane(dsc.w);
   const int G = a.n_q / a.n_kv;
 
-  bf16x8_t qf[KS];
-  if (c < G) {  // k-step ks, lane group g: dimensions 32ks + 8g .. +7, the K cache's order
-    const bf16_t* qrow = static_cast<const bf16_t*>(a.q) + (static_cast<size_t>(b) * a.n_q + kh * G + c) * HD + g * 8;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[ks] = load_bf16x8(qrow + ks * 32);
-  } else {
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[ks] = __builtin_bit_cast(bf16x8_t, make_uint4(0, 0, 0, 0));
-  }
   // Lane i holds the page of the item's i-th page (the first 64 pages; later
   // ones, for items longer than 4096 tokens, are read from the table).
   const int* pt = a.page_table + static_cast<size_t>(slot) * a.pt_stride;
@@ -76,16 +100,81 @@ __global__ __launch_bounds__(64) void k_attn_decode_bf16(AttnArgs a) {
   const int npg = (t1 + kPageTokens - 1) / kPageTokens - p0;
   const int ptv = lane < npg ? pt[p0 + lane] : 0;
   const int u0 = t0 >> 5;
-  const int nu = ((t1 + 31) >> 5) - u0;  // half pages of the item
+  const int nu = ((t1 + 31) >> 5) - u0;           // half pages of the item (>= 1)
+  const int nw = nu > wave ? (nu - wave + NW - 1) / NW : 0;  // this wave's: wave, wave + NW, ...
   const bf16_t* kpool = static_cast<const bf16_t*>(a.k_pool);
   const bf16_t* vpool = static_cast<const bf16_t*>(a.v_pool);
   const float scale_log2 = a.scale * kLog2e;
 
+  // Prologue items: G * HALF query pairs, then (append) HALF key pairs and HD values.  A thread's first
+  // two are loaded, up to kEarly partials each, before the K/V loads are issued and used after: loads
+  // complete in order, so the rotation does not wait for K/V.
+  constexpr int kEarly = 4;
+  const RopeArgs& ra = a.rope;
+  const int pos = ra.pos[b];
+  const int nqkv = (a.n_q + 2 * a.n_kv) * HD;
+  const size_t plane = static_cast<size_t>(ra.M) * nqkv;
+  const float* __restrict__ prow = ra.part + static_cast<size_t>(b) * nqkv;
+  const int n_pairs = (G + (append ? 1 : 0)) * HALF, n_work = n_pairs + (append ? HD : 0);
+  struct Item {
+    float p1[kEarly], p2[kEarly], cs, sn;
+    uint32_t b1, b2;
+  };
+  auto column = [&](int w) {  // of the projection: the pair's first, or the value's
+    if (w < G * HALF) return (kh * G + w / HALF) * HD + w % HALF;
+    return w < n_pairs ? (a.n_q + kh) * HD + w % HALF : (a.n_q + a.n_kv + kh) * HD + w - n_pairs;
+  };
+  auto fetch = [&](int w, Item& it) {  // no branches: an item past the last re-reads it
+    w = min(w, n_work - 1);
+    const int n = column(w), n2 = w < n_pairs ? n + HALF : n, d = w % HALF;
+#pragma unroll
+    for (int s = 0; s < kEarly; ++s) {
+      const float* p = prow + min(s, ra.splits - 1) * plane;
+      it.p1[s] = p[n];
+      it.p2[s] = p[n2];
+    }
+    const bf16_t* bias = w < G * HALF   ? static_cast<const bf16_t*>(ra.bq) + n
+                         : w < n_pairs ? static_cast<const bf16_t*>(ra.bk) + n - a.n_q * HD
+                                       : static_cast<const bf16_t*>(ra.bv) + n - (a.n_q + a.n_kv) * HD;
+    it.b1 = bias[0];
+    it.b2 = bias[n2 - n];
+    it.cs = ra.rope_cos[static_cast<size_t>(pos) * HALF + d];
+    it.sn = ra.rope_sin[static_cast<size_t>(pos) * HALF + d];
+  };
+  auto finish = [&](int w, const Item& it) {
+    if (w >= n_work) return;
+    const int n = column(w), n2 = w < n_pairs ? n + HALF : n, d = w % HALF;
+    float v1 = 0.f, v2 = 0.f;
+#pragma unroll
+    for (int s = 0; s < kEarly; ++s)
+      if (s < ra.splits) {
+        v1 += it.p1[s];
+        v2 += it.p2[s];
+      }
+    for (int s = kEarly; s < ra.splits; ++s) {
+      v1 += prow[s * plane + n];
+      v2 += prow[s * plane + n2];
+    }
+    v1 += bf16_to_f32(static_cast<bf16_t>(it.b1));
+    v2 += bf16_to_f32(static_cast<bf16_t>(it.b2));
+    if (w < n_pairs) {
+      bf16_t* dst = w < G * HALF ? sq + (w / HALF) * HD : snk;
+      dst[d] = f32_to_bf16(v1 * it.cs - v2 * it.sn);
+      dst[d + HALF] = f32_to_bf16(v2 * it.cs + v1 * it.sn);
+    } else {
+      snv[w - n_pairs] = f32_to_bf16(v1);
+    }
+  };
+  Item it0, it1;
+  fetch(tid, it0);
+  fetch(tid + 64 * NW, it1);
+  __builtin_amdgcn_sched_barrier(0);
+
   bf16x8_t kf[D][2][KS], vf[D][NB];
-  auto load = [&](int sl, int i) {
-    const int u = u0 + min(i, nu - 1);  // prologue stages past the item re-read its last half page
+  auto load = [&](int sl, int i, auto first) {
+    const int u = u0 + min(wave + NW * i, nu - 1);  // stages past the wave's share re-read the item's last half page
     const int pi = (u >> 1) - p0;
-    const int pg = pi < 64 ? __builtin_amdgcn_readlane(ptv, pi) : pt[p0 + pi];
+    const int pg = first.value || pi < 64 ? __builtin_amdgcn_readlane(ptv, pi) : pt[p0 + pi];
     const int h = u & 1;
     const size_t pb = (static_cast<size_t>(pg) * a.n_kv + kh) * kPageTokens * HD;
 #pragma unroll
@@ -100,19 +189,37 @@ __global__ __launch_bounds__(64) void k_attn_decode_bf16(AttnArgs a) {
 #pragma unroll
     for (int blk = 0; blk < NB; ++blk) vf[sl][blk] = load_bf16x8_nt(vh + (blk * 16 + c) * 32 + 8 * g);
   };
+  // Unconditional prologue and scheduling barriers: every path into the
+  // main loop has the same loads in flight, so its wait counts are exact.
+#pragma unroll
+  for (int s = 0; s < D; ++s) {
+    load(s, s, std::true_type{});
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  finish(tid, it0);
+  finish(tid + 64 * NW, it1);
+  for (int w = tid + 128 * NW; w < n_work; w += 64 * NW) {
+    fetch(w, it0);
+    finish(w, it0);
+  }
+  __syncthreads();
+  bf16x8_t qf[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks)  // k-step ks, lane group g: dimensions 32ks + 8g .. +7, the K cache's order
+    qf[ks] = c < G ? load_bf16x8(sq + c * HD + ks * 32 + g * 8) : __builtin_bit_cast(bf16x8_t, make_uint4(0, 0, 0, 0));
 
   f32x4_t o[NB];
 #pragma unroll
   for (int blk = 0; blk < NB; ++blk) o[blk] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY, l_run = 0.f;
-  auto compute = [&](int sl, int i) {
-    const int u = u0 + i;
+  // One half page whose first token is tok0; keys at t_end and past it are masked.
+  auto attend = [&](const bf16x8_t (&kk)[2][KS], const bf16x8_t (&vv)[NB], int tok0, int t_end) {
     f32x4_t sacc[2];
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt) {
       sacc[tt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) sacc[tt] = mfma16x16x32(kf[sl][tt][ks], qf[ks], sacc[tt]);
+      for (int ks = 0; ks < KS; ++ks) sacc[tt] = mfma16x16x32(kk[tt][ks], qf[ks], sacc[tt]);
     }
     float sv[8];
     float pmax = -INFINITY;
@@ -120,9 +227,8 @@ __global__ __launch_bounds__(64) void k_attn_decode_bf16(AttnArgs a) {
     for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int tok = 32 * u + 8 * g + 4 * tt + e;
         float v = sacc[tt][e] * scale_log2;
-        if (tok < t0 || tok >= t1) v = -INFINITY;
+        if (tok0 + 8 * g + 4 * tt + e >= t_end) v = -INFINITY;
         sv[tt * 4 + e] = v;
         pmax = fmaxf(pmax, v);
       }
@@ -142,65 +248,97 @@ __global__ __launch_bounds__(64) void k_attn_decode_bf16(AttnArgs a) {
     l_run = l_run * alpha + psum;
     m_run = m_new;
     uint4 w;
-    w.x = static_cast<uint32_t>(f32_to_bf16(sv[0])) | (static_cast<uint32_t>(f32_to_bf16(sv[1])) << 16);
-    w.y = static_cast<uint32_t>(f32_to_bf16(sv[2])) | (static_cast<uint32_t>(f32_to_bf16(sv[3])) << 16);
-    w.z = static_cast<uint32_t>(f32_to_bf16(sv[4])) | (static_cast<uint32_t>(f32_to_bf16(sv[5])) << 16);
-    w.w = static_cast<uint32_t>(f32_to_bf16(sv[6])) | (static_cast<uint32_t>(f32_to_bf16(sv[7])) << 16);
+    w.x = pack_bf16x2(sv[0], sv[1]);
+    w.y = pack_bf16x2(sv[2], sv[3]);
+    w.z = pack_bf16x2(sv[4], sv[5]);
+    w.w = pack_bf16x2(sv[6], sv[7]);
     const bf16x8_t pf = __builtin_bit_cast(bf16x8_t, w);
 #pragma unroll
-    for (int blk = 0; blk < NB; ++blk) o[blk] = mfma16x16x32(vf[sl][blk], pf, o[blk] * alpha);
+    for (int blk = 0; blk < NB; ++blk) o[blk] = mfma16x16x32(vv[blk], pf, o[blk] * alpha);
   };
+  auto compute = [&](int sl, int i) { attend(kf[sl], vf[sl], 32 * (u0 + wave + NW * i), t1); };
 
-  if (nu > 0) {
-    // Unconditional prologue and scheduling barriers: every path into the
-    // main loop has the same loads in flight, so its wait counts are exact.
+  int i = 0;
+  for (; i + 2 * D <= nw; i += D) {
 #pragma unroll
-    for (int sl = 0; sl < D; ++sl) {
-      load(sl, sl);
+    for (int s = 0; s < D; ++s) {
+      compute(s, i + s);
+      __builtin_amdgcn_sched_barrier(0);
+      load(s, i + s + D, std::false_type{});
       __builtin_amdgcn_sched_barrier(0);
     }
-    int i = 0;
-    for (; i + 2 * D <= nu; i += D) {
+  }
 #pragma unroll
-      for (int sl = 0; sl < D; ++sl) {
-        compute(sl, i + sl);
-        __builtin_amdgcn_sched_barrier(0);
-        load(sl, i + sl + D);
-        __builtin_amdgcn_sched_barrier(0);
-      }
+  for (int j = 0; j < 2 * D; ++j) {
+    if (i + j < nw) {
+      compute(j % D, i + j);
+      __builtin_amdgcn_sched_barrier(0);
+      if (i + j + D < nw) load(j % D, i + j + D, std::false_type{});
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  if (append && wave == nu % NW) {
+    // The newest token, as a half page of which only token 0 (row 0 of tile 0) is a key.
+    const uint4 zero = make_uint4(0, 0, 0, 0);
+    bf16x8_t nk[2][KS], nv[NB];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      nk[0][ks] = c == 0 ? load_bf16x8(snk + ks * 32 + g * 8) : __builtin_bit_cast(bf16x8_t, zero);
+      nk[1][ks] = __builtin_bit_cast(bf16x8_t, zero);
     }
 #pragma unroll
-    for (int j = 0; j < 2 * D; ++j) {
-      if (i + j < nu) {
-        compute(j % D, i + j);
-        __builtin_amdgcn_sched_barrier(0);
-        if (i + j + D < nu) load(j % D, i + j + D);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
+    for (int blk = 0; blk < NB; ++blk)
+      nv[blk] = __builtin_bit_cast(bf16x8_t, make_uint4(g == 0 ? snv[blk * 16 + c] : 0, 0, 0, 0));
+    attend(nk, nv, 0, 1);
+    // append: K in MFMA operand order (16-byte runs of eight dimensions), V [hd][32 tokens] per half page
+    const int off = pos % kPageTokens;
+    const size_t blk0 = (static_cast<size_t>(pt[pos / kPageTokens]) * a.n_kv + kh) * kPageTokens * HD;
+    if (lane < HD / 8)
+      *reinterpret_cast<bf16x8_t*>(static_cast<bf16_t*>(ra.k_pool) + blk0 + k_page_offset(off, lane * 8, HD)) = load_bf16x8(snk + lane * 8);
+#pragma unroll
+    for (int d = lane; d < HD; d += 64)
+      static_cast<bf16_t*>(ra.v_pool)[blk0 + (off >> 5) * HD * 32 + d * 32 + (off & 31)] = snv[d];
   }
 
-  if (c >= G) return;
-  if (single) {  // the row's only split: normalise and write the output directly
-    const float inv = 1.f / l_run;
-    bf16_t* orow = static_cast<bf16_t*>(a.out) + (static_cast<size_t>(b) * a.n_q + kh * G + c) * HD;
-#pragma unroll
-    for (int blk = 0; blk < NB; ++blk) {
-      uint2 pk;
-      pk.x = static_cast<uint32_t>(f32_to_bf16(o[blk][0] * inv)) | (static_cast<uint32_t>(f32_to_bf16(o[blk][1] * inv)) << 16);
-      pk.y = static_cast<uint32_t>(f32_to_bf16(o[blk][2] * inv)) | (static_cast<uint32_t>(f32_to_bf16(o[blk][3] * inv)) << 16);
-      *reinterpret_cast<uint2*>(orow + blk * 16 + 4 * g) = pk;
-    }
-    return;
-  }
-  const size_t item = static_cast<size_t>(x) * a.n_kv + kh;
-  float* po = a.part_o + (item * 16 + c) * HD;
-#pragma unroll
-  for (int blk = 0; blk < NB; ++blk)
-    *reinterpret_cast<float4*>(po + blk * 16 + 4 * g) = make_float4(o[blk][0], o[blk][1], o[blk][2], o[blk][3]);
+  // Combine the waves' states: a wave without a half page has m = -inf, l = 0, o = 0.
   if (g == 0) {
-    a.part_ml[item * 32 + c] = m_run;
-    a.part_ml[item * 32 + 16 + c] = l_run;
+    sm[wave][c] = m_run;
+    sl[wave][c] = l_run;
+  }
+  __syncthreads();
+  float mx = sm[0][c];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) mx = fmaxf(mx, sm[w][c]);
+  const float f = m_run == -INFINITY ? 0.f : exp2f(m_run - mx);
+  if (c < G) {
+#pragma unroll
+    for (int blk = 0; blk < NB; ++blk) *reinterpret_cast<f32x4_t*>(&so[wave][c * OLD + blk * 16 + 4 * g]) = o[blk] * f;
+  }
+  __syncthreads();
+  for (int q = tid; q < G * (HD / 4); q += 64 * NW) {
+    const int cc = q / (HD / 4), d = (q % (HD / 4)) * 4;
+    float m4 = sm[0][cc], den = 0.f;
+#pragma unroll
+    for (int w = 1; w < NW; ++w) m4 = fmaxf(m4, sm[w][cc]);
+#pragma unroll
+    for (int w = 0; w < NW; ++w) den += sm[w][cc] == -INFINITY ? 0.f : sl[w][cc] * exp2f(sm[w][cc] - m4);
+    f32x4_t v = *reinterpret_cast<const f32x4_t*>(&so[0][cc * OLD + d]);
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v += *reinterpret_cast<const f32x4_t*>(&so[w][cc * OLD + d]);
+    if (single) {  // the row's only item: normalise and write the output directly
+      const float inv = 1.f / den;
+      uint2 pk;
+      pk.x = static_cast<uint32_t>(f32_to_bf16(v[0] * inv)) | (static_cast<uint32_t>(f32_to_bf16(v[1] * inv)) << 16);
+      pk.y = static_cast<uint32_t>(f32_to_bf16(v[2] * inv)) | (static_cast<uint32_t>(f32_to_bf16(v[3] * inv)) << 16);
+      *reinterpret_cast<uint2*>(static_cast<bf16_t*>(a.out) + (static_cast<size_t>(b) * a.n_q + kh * G + cc) * HD + d) = pk;
+    } else {
+      const size_t pi = static_cast<size_t>(a.split_off[b] + t0 / a.tokens_per_split) * a.n_kv + kh;
+      *reinterpret_cast<f32x4_t*>(a.part_o + (pi * 16 + cc) * HD + d) = v;
+      if (d == 0) {
+        a.part_ml[pi * 32 + cc] = m4;
+        a.part_ml[pi * 32 + 16 + cc] = den;
+      }
+    }
   }
 }
 
@@ -346,15 +484,6 @@ __global__ __launch_bounds__(64) void k_attn_merge_few(AttnArgs a) {
 constexpr int kPrefillWaveGroups = 1;
 constexpr int kPrefillWaves = 8;
 constexpr int kMaxContextPages = 65536 / kPageTokens;  // the engine's context limit
-
-typedef __bf16 bf16x2_hw __attribute__((ext_vector_type(2)));
-typedef float f32x2_hw __attribute__((ext_vector_type(2)));
-
-// Two fp32 values to packed bf16, round to nearest even (gfx950's v_cvt_pk_bf16_f32; for the
-// finite values here the same result as f32_to_bf16).
-__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_hw{lo, hi}, bf16x2_hw));
-}
 
 // One page step of the prefill kernel for a wave's NG query groups.  MASKED: whether any key
 // of the page may lie past some column's own position (the diagonal pages); the others are
@@ -696,9 +825,9 @@ hipError_t launch_attn_decode(int bf16, const AttnArgs& a, hipStream_t s) {
   }
   if (a.B <= 0 || a.total_splits <= 0) return hipSuccess;
   if (a.n_q / a.n_kv > 16 || a.tokens_per_split % kPageTokens != 0 || !a.split_desc) return hipErrorInvalidValue;
-  dim3 grid(a.total_splits, a.n_kv);
-  if (a.hd == 128) launch_kernel(k_attn_decode_bf16<128>, grid, dim3(64), 0, s, a);
-  else if (a.hd == 64) launch_kernel(k_attn_decode_bf16<64>, grid, dim3(64), 0, s, a);
+  dim3 grid(a.total_splits * a.n_kv);
+  if (a.hd == 128) launch_kernel(k_attn_decode_bf16<128>, grid, dim3(64 * kDecodeWaves), 0, s, a);
+  else if (a.hd == 64) launch_kernel(k_attn_decode_bf16<64>, grid, dim3(64 * kDecodeWaves), 0, s, a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

@@ -135,7 +135,10 @@ struct AttnArgs {
   int B; const int32_t* row_slot; const int32_t* row_ctx; const int32_t* split_off;
   int total_splits; int tokens_per_split;
   int max_row_splits;             // most splits of any row (0: unknown); picks the merge kernel
-  const int32_t* split_desc;      // [total_splits, 4]: row (+ 2^30 if its only split), first key, end key, slot
+  // [total_splits, 4]: row (+ 2^30 if its only split, + 2^29 if it holds the row's newest token), first
+  // and end cached key, slot; the longest first
+  const int32_t* split_desc;
+  RopeArgs rope;                  // bf16 decode: q/k/v partials, bias, tables and append target
   float* part_o; float* part_ml;  // [total_splits * n_kv, 16, hd], [.., 2, 16]
   // prefill (causal over packed prompt chunks):
   int n_seq; const int32_t* seq_slot; const int32_t* seq_row0; const int32_t* seq_pos0;

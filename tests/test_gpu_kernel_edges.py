@@ -67,3 +67,21 @@ def test_fp32_model_edges(hd, inter, vocab, plens):
     products of either order agree to about 1e-6; the bar is the fp32 model's 1e-4."""
     shape = ModelShape("f32", 2, 132, 6, 2, hd, inter, vocab, False, "f32")
     _parity(shape, plens, 3, max_prefill=2048, tol=1e-4)
+
+
+@pytest.mark.parametrize("n_q,n_kv,hd,plens", [
+    (14, 2, 64, [1, 31, 32, 33, 62, 63, 64, 65, 126, 127, 128, 129]),  # half-page and page edges, one item a row
+    (7, 1, 128, [255, 256, 257, 511, 640, 1]),                         # several half pages a wave
+    (16, 1, 64, [64, 40]),                                             # 16 query heads: every column used
+    (3, 3, 128, [130, 2]),                                             # one query head per KV head
+    (14, 2, 64, [2300] + [5, 64] * 3),                                 # a long row in items beside single ones
+    (4, 4, 128, [1500, 1400, 63]),                                     # few rows: items and the 1024-thread merge
+])
+def test_decode_attention_edges(n_q, n_kv, hd, plens):
+    """Decode attention items: cached keys ending on and beside half pages and pages (the newest
+    token opens a page), waves without a half page, one to sixteen query heads per KV head, rows of
+    one item and of several, which the merge combines."""
+    shape = ModelShape("attn", 1, 384, n_q, n_kv, hd, 256, 640, False, "bf16")
+    if (n_q + 2 * n_kv) * hd % 128 or n_q * hd % 128:
+        shape = dataclasses.replace(shape, n_q=n_q, head_dim=128)
+    _parity(shape, plens, 3, max_prefill=4096)
