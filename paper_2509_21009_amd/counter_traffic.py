@@ -6,8 +6,8 @@ and four 16-row activation tiles), and the ``--kernel-trace --stats``
 kernel_stats CSV of the benchmark round whose launch mix weights them.  Each
 profile_steps run ends with a 1 GiB device copy; its counter readings
 calibrate FETCH_SIZE and WRITE_SIZE (KiB per dispatch) to bytes.  Writes the
-record bench.py reads (kernel, workload, SHA-256 of the deep kernel's source
-text and launch plan, bytes per launch) and prints a table for the profile summary.  From the repository
+record bench.py reads (kernel, workload, SHA-256 of the decode kernels' source
+text and launch plans, bytes per launch) and prints a table for the profile summary.  From the repository
 root:
 
     python3 paper_2509_21009_amd/counter_traffic.py --pmc-dir results/pmc \\
@@ -34,13 +34,16 @@ def _between(text: str, start: str, end: str) -> str:
 
 
 def deep_source_digest(root: str = ROOT) -> str:
-    """SHA-256 over what the counters measured: the k_gemm_deep kernel and its weight-load helper,
-    its launch plan (the instantiated configurations and plan_deep) and the device helpers it uses.  Edits elsewhere in
-    the GEMM source leave it unchanged."""
+    """SHA-256 over what the counters measured: the k_gemm_deep and k_gemm_ring kernels, their launch
+    plans (plan_deep with the instantiated configurations, plan_ring) and the device helpers they use.
+    Edits elsewhere in the GEMM source leave it unchanged."""
     gemm = open(os.path.join(root, SOURCE)).read()
     parts = [_between(gemm, "template <bool PACKED>\n__device__ __forceinline__ bf16x8_t load_w16", "\n}\n"),
              _between(gemm, "template <int R, int MT, int D, bool SILU, bool PACKED>\n__global__ __launch_bounds__(256) "
                             "void k_gemm_deep", "\n}\n"),
+             _between(gemm, "template <int R, int MT, bool SILU, bool PACKED>\n__global__ __launch_bounds__(256) "
+                            "void k_gemm_ring", "\n}\n"),
+             _between(gemm, "GemmPlan plan_ring(", "\n}\n"),
              _between(gemm, "constexpr DeepCfg kDeepCfg", "\n};\n"),
              _between(gemm, "GemmPlan plan_deep(", "\n}\n"),
              open(os.path.join(root, COMMON)).read()]
@@ -50,8 +53,9 @@ SHAPE = {"H": 3584, "I": 18944}  # Qwen2.5-7B hidden and intermediate sizes
 
 
 def gate_up_tiles(name: str):
-    """Activation tiles of a gate/up (SiLU) deep-GEMM instantiation, else None."""
-    m = re.search(r"k_gemm_deep<(\d+), (\d+), (\d+), true(?:, (?:true|false))?>", name)
+    """Activation tiles of a gate/up (SiLU) decode-GEMM instantiation, else None."""
+    m = (re.search(r"k_gemm_deep<(\d+), (\d+), (\d+), true(?:, (?:true|false))?>", name) or
+         re.search(r"k_gemm_ring<(\d+), (\d+), true, (?:true|false)>", name))
     return int(m.group(2)) if m else None
 
 

@@ -6,7 +6,7 @@
 // accumulation and W as the 16-row "A" operand, activations as the
 // 16-column "B" operand, so one MFMA yields a [16 n, 16 m] tile of C^T.
 //
-//  * k_gemm_deep (M <= 64, the decode regime, most shapes): weights stream
+//  * k_gemm_deep (M <= 16, large weight matrices): weights stream
 //    from HBM through buffer loads into a ring of register stages; a stage
 //    is a 64-wide K unit in which each lane reads 32 contiguous bytes of a
 //    row, so one wave's two back-to-back loads cover the row's whole
@@ -15,12 +15,15 @@
 //    (the weights are read once per step), the same operands in every lane.  Activations (L2-resident) are loaded one stage ahead
 //    into a single buffer.  The block's 4 waves take interleaved K units and
 //    reduce through LDS; blockIdx.y splits K further (fp32 partials).
-//  * k_gemm_stream (M <= 64, the remaining decode shapes): the weights are streamed
+//  * k_gemm_ring (17-64 rows, and the largest products of fewer): the same split of
+//    the work, weights and activations copied into per-wave LDS rings.
+//  * k_gemm_stream, k_gemm_skinny (M <= 16, small matrices): the weights are streamed
 //    once from HBM straight into registers; every lane loads 64 contiguous
 //    bytes per row per 128-wide K chunk (the K order inside a chunk is
 //    permuted identically for both operands, which leaves the dot products
-//    unchanged).  The 4 waves of a block split the chunk range and reduce
-//    through LDS; blockIdx.y splits K further and writes fp32 partials that
+//    unchanged).  The 4 waves of a k_gemm_stream block split the chunk range and reduce
+//    through LDS, those of a k_gemm_skinny block own different rows and share the
+//    activations; blockIdx.y splits K further and writes fp32 partials that
 //    the consumer kernel sums.
 //  * k_gemm_tiled (M > 64: prefill and large decode batches): 128- or
 //    256-row x 128- or 256-row block tiles of 32x32x16 MFMAs, half tiles
@@ -473,6 +476,184 @@ __global__ __launch_bounds__(256) void k_gemm_deep(GemmArgs a, int units_per_spl
   }
 }
 
+// ---- decode-regime weight streaming through private LDS rings ---------------
+// k_gemm_deep's work split (4 waves on the same R weight fragments, K units
+// interleaved over the waves, no barrier until the end) for 17-64 activation
+// rows.  There a register ring starves: a stage's MFMAs and the wait for the
+// next stage's activations run while one stage of weights is in flight (R = 10
+// fragments x 4 activation tiles leave no registers for more), and gate/up of
+// the 7B took 62 us at 64 rows against 46 at 16.  Here weights and activations are copied
+// into LDS (buffer_load ... lds), 40 KB per wave: two units of activations and a
+// ring of the next 12-16 weight fragments, each refilled as soon as it is in
+// registers, so about 30 KB per wave stay in flight whatever the MFMAs do.  A wave
+// waits for its own copies by count (they complete in order) and reads a
+// fragment while the MFMAs of the one before run.  Copies past the wave's last
+// unit are out of the resource's range: they move nothing and keep the counts.
+// Gate/up of the 7B streams its packed weights at 5.7-6.0 TB/s from 1 to 64 rows
+// (45.0-47.6 us).  The non-temporal mark on the packed copies is worth 10%
+// (54 us without it at 64 rows).
+template <int R, int MT, bool SILU, bool PACKED>
+__global__ __launch_bounds__(256) void k_gemm_ring(GemmArgs a, int units_per_split) {
+  static_assert(R % 2 == 0, "register buffers alternate by fragment; SiLU pairs gate and up fragments");
+  constexpr int WAVE_LDS = 40960, A_UNIT = MT * 2048, SLOTS = (WAVE_LDS - 2 * A_UNIT) / 2048;
+  static_assert(SLOTS >= R, "the counts below assume that a unit's fragments fit the ring");
+  static_assert(4 * R * MT * 1024 <= 4 * WAVE_LDS, "the final reduction reuses the rings");
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[4 * WAVE_LDS];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, r = lane & 15;
+  const int K = a.K, KU = K / 64;
+  const int u0 = blockIdx.y * units_per_split;
+  const int u1 = min(u0 + units_per_split, KU);
+  const int nblk = max(u1 - u0, 0);
+  const int nk = nblk > wave ? (nblk - wave + 3) / 4 : 0;
+  const uint32_t row_bytes = static_cast<uint32_t>(K) * 2u;
+
+  const WSeg& W = PACKED ? a.Wp : a.W;
+  u32x4_raw rw[R];
+#pragma unroll
+  for (int t = 0; t < R; ++t) {
+    const bf16_t* base;
+    int valid;
+    if (SILU) {
+      const int row0 = (blockIdx.x * (R / 2) + t % (R / 2)) * 16;
+      valid = row0 < a.N ? min(16, a.N - row0) : 0;
+      base = static_cast<const bf16_t*>(W.ptr[t / (R / 2)]) + static_cast<size_t>(valid ? row0 : 0) * K;
+    } else {
+      const int row0 = (blockIdx.x * R + t) * 16;
+      int b = 0, sg = 0;
+      while (sg < W.n_seg - 1 && row0 >= b + W.rows[sg]) b += W.rows[sg++];
+      valid = row0 < a.N ? min(16, W.rows[sg] - (row0 - b)) : 0;
+      base = static_cast<const bf16_t*>(W.ptr[sg]) + static_cast<size_t>(valid ? row0 - b : 0) * K;
+    }
+    // a packed tile is whole (16 rows) or absent; a row-major one may be ragged
+    rw[t] = raw_rsrc(base, static_cast<uint32_t>(PACKED ? (valid ? 16 : 0) : valid) * row_bytes);
+  }
+  // rows m >= M of the activations read as zeros
+  const u32x4_raw ra = raw_rsrc(a.A, static_cast<uint32_t>(a.M) * static_cast<uint32_t>(a.lda) * 2u);
+
+  // A row-major copy instruction takes 8 rows of one 128-byte line; LDS chunk lane & 7 of a row holds
+  // global chunk (lane & 7) ^ ((row >> 1) & 7), which keeps the fragment reads free of bank conflicts.
+  // A packed one takes 1 KB of a tile's 2 KB unit run.
+  const int c8 = lane >> 3, ch = lane & 7;
+  typedef const __attribute__((address_space(3))) char lds_char;
+  const uint32_t lds0 = static_cast<uint32_t>((uintptr_t)(lds_char*)(smem)) + static_cast<uint32_t>(wave * WAVE_LDS);
+  constexpr int kOut = 0x40000000;  // past every resource
+  int aoff[2], woff[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int row = h * 8 + c8, gc = ch ^ ((row >> 1) & 7);
+    aoff[h] = row * static_cast<int>(a.lda) * 2 + (u0 + wave) * 128 + gc * 16;
+    woff[h] = PACKED ? (u0 + wave) * 2048 + h * 1024 + lane * 16
+                     : row * static_cast<int>(row_bytes) + (u0 + wave) * 128 + gc * 16;
+  }
+  const int lda16 = 16 * static_cast<int>(a.lda) * 2;
+  auto copy_a = [&](int i) {  // unit i of the wave into activation buffer i & 1
+    const int o = i < nk ? i * 512 : kOut;
+    const uint32_t dst = __builtin_amdgcn_readfirstlane(lds0 + static_cast<uint32_t>((i & 1) * A_UNIT));
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) dma16(ra, dst + mt * 2048 + h * 1024, aoff[h] + mt * lda16 + o);
+  };
+  auto copy_w = [&](int t, int i, int slot) {  // fragment t of the wave's unit i into a ring slot
+    const int o = i < nk ? i * (PACKED ? 4 * 2048 : 512) : kOut;
+    const uint32_t dst = __builtin_amdgcn_readfirstlane(lds0 + static_cast<uint32_t>(2 * A_UNIT + slot * 2048));
+    if (PACKED) {
+      dma16_nt(rw[t], dst, woff[0] + o);
+      dma16_nt(rw[t], dst + 1024, woff[1] + o);
+    } else {
+      dma16(rw[t], dst, woff[0] + o);
+      dma16(rw[t], dst + 1024, woff[1] + o);
+    }
+  };
+  const int rsw = (r >> 1) & 7;
+  const int rd_row[2] = {r * 128 + ((2 * g) ^ rsw) * 16, r * 128 + ((2 * g + 1) ^ rsw) * 16};
+  const uint8_t* base = smem + wave * WAVE_LDS;
+  bf16x8_t av[MT][2], wv[2][2];
+  auto read_a = [&](int i) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        av[mt][j] = *reinterpret_cast<const bf16x8_t*>(base + (i & 1) * A_UNIT + mt * 2048 + rd_row[j]);
+  };
+  auto read_w = [&](int buf, int slot) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      wv[buf][j] = *reinterpret_cast<const bf16x8_t*>(base + 2 * A_UNIT + slot * 2048 + (PACKED ? j * 1024 + lane * 16 : rd_row[j]));
+  };
+
+  f32x4_t acc[R][MT];
+#pragma unroll
+  for (int t = 0; t < R; ++t)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[t][mt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  constexpr int kLgkm0 = 0xc07f;  // s_waitcnt lgkmcnt(0)
+  copy_a(0);
+  copy_a(1);
+#pragma unroll
+  for (int f = 0; f < SLOTS; ++f) copy_w(f % R, f / R, f);
+  wait_vmcnt<2 * (SLOTS - 1)>();  // fragment 0, and with it both activation units
+  read_w(0, 0);
+  __builtin_amdgcn_s_waitcnt(kLgkm0);
+  copy_w(SLOTS % R, SLOTS / R, 0);
+  int slot = 0;
+  for (int i = 0; i < nk; ++i) {
+    // activations of unit i: after them, those of unit i + 1 and two units of fragments were issued
+    wait_vmcnt<4 * R + 2 * MT>();
+    read_a(i);
+    __builtin_amdgcn_s_waitcnt(kLgkm0);
+    copy_a(i + 2);
+#pragma unroll
+    for (int t = 0; t < R; ++t) {
+      // the next fragment: after it, SLOTS - 1 fragments and at least one activation unit were issued
+      wait_vmcnt<2 * (SLOTS - 1) + 2 * MT>();
+      slot = slot + 1 == SLOTS ? 0 : slot + 1;
+      read_w((t + 1) & 1, slot);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) acc[t][mt] = mfma16x16x32(wv[t & 1][j], av[mt][j], acc[t][mt]);
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_waitcnt(kLgkm0);
+      copy_w((t + 1 + SLOTS) % R, i + (t + 1 + SLOTS) / R, slot);
+    }
+  }
+  wait_vmcnt<0>();  // no copy may land in LDS from here on
+  __syncthreads();
+  f32x4_t* red = reinterpret_cast<f32x4_t*>(smem);
+#pragma unroll
+  for (int t = 0; t < R; ++t)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) red[((t * MT + mt) * 4 + wave) * 64 + lane] = acc[t][mt];
+  __syncthreads();
+  // lane (g, r) of accumulator (t, mt) holds C^T[row base + t*16 + 4g + e][m = mt*16 + r]
+  auto total = [&](int t, int mt) {
+    const f32x4_t* p = red + (t * MT + mt) * 4 * 64 + lane;
+    return p[0] + p[64] + p[128] + p[192];
+  };
+  for (int q = wave; q < (SILU ? R / 2 : R) * MT; q += 4) {
+    const int t = q / MT, mt = q % MT, m = mt * 16 + r;
+    if (m >= a.M) continue;
+    if (SILU) {
+      const int i0 = (blockIdx.x * (R / 2) + t) * 16 + g * 4;
+      if (i0 >= a.N) continue;
+      const f32x4_t gv = total(t, mt), uv = total(t + R / 2, mt);
+      uint2 pk;
+      pk.x = static_cast<uint32_t>(bf16_of(silu_fast(gv[0]) * uv[0])) | (static_cast<uint32_t>(bf16_of(silu_fast(gv[1]) * uv[1])) << 16);
+      pk.y = static_cast<uint32_t>(bf16_of(silu_fast(gv[2]) * uv[2])) | (static_cast<uint32_t>(bf16_of(silu_fast(gv[3]) * uv[3])) << 16);
+      *reinterpret_cast<uint2*>(static_cast<bf16_t*>(a.act_out) + static_cast<size_t>(m) * a.N + i0) = pk;
+    } else {
+      const int n = (blockIdx.x * R + t) * 16 + g * 4;
+      if (n >= a.N) continue;
+      *reinterpret_cast<f32x4_t*>(a.part + (static_cast<size_t>(blockIdx.y) * a.M + m) * a.N + n) = total(t, mt);
+    }
+  }
+}
+
 // ---- prefill / large-batch tiled MFMA GEMM ---------------------------------
 // Block tile: BM activation rows (m, 128 or 256) x BN weight rows (n, 128 or
 // 256), K step 64, on v_mfma_f32_32x32x16_bf16.  Activations are the MFMA row
@@ -826,64 +1007,72 @@ void launch_f32(const GemmArgs& a, hipStream_t s) {
   else launch_f32_t<4, SILU>(a, s);
 }
 
-template <int R, int MT, bool SILU>
-void launch_stream_t(const GemmArgs& a, hipStream_t s) {
-  const int n_chunks = a.K / 128;
-  const int cps = (n_chunks + a.splits - 1) / a.splits;
-  const int blocks = SILU ? a.N / 16 : a.N / (16 * R);
-  launch_kernel((k_gemm_stream<R, MT, SILU>), dim3(blocks, a.splits), dim3(256), 0, s, a, cps);
-}
-
 template <bool SILU>
-void launch_stream_m(const GemmArgs& a, hipStream_t s) {
-  switch ((a.M + 15) / 16) {
-    case 1: launch_stream_t<2, 1, SILU>(a, s); break;
-    case 2: launch_stream_t<2, 2, SILU>(a, s); break;
-    case 3: launch_stream_t<2, 3, SILU>(a, s); break;
-    default: launch_stream_t<2, 4, SILU>(a, s); break;
-  }
-}
-
-template <int R, int MT, bool SILU>
-void launch_skinny_t(const GemmArgs& a, hipStream_t s) {
+void launch_stream(const GemmArgs& a, hipStream_t s) {
   const int n_chunks = a.K / 128;
   const int cps = (n_chunks + a.splits - 1) / a.splits;
-  const int blocks = SILU ? a.N / 64 : a.N / (64 * R);
-  launch_kernel((k_gemm_skinny<R, MT, SILU>), dim3(blocks, a.splits), dim3(256), 0, s, a, cps);
+  const int blocks = SILU ? a.N / 16 : a.N / 32;
+  launch_kernel((k_gemm_stream<2, 1, SILU>), dim3(blocks, a.splits), dim3(256), 0, s, a, cps);
 }
 
-template <int R, bool SILU>
-void launch_skinny_m(const GemmArgs& a, hipStream_t s) {
-  switch ((a.M + 15) / 16) {
-    case 1: launch_skinny_t<R, 1, SILU>(a, s); break;
-    case 2: launch_skinny_t<R, 2, SILU>(a, s); break;
-    case 3: launch_skinny_t<R, 3, SILU>(a, s); break;
-    default: launch_skinny_t<R, 4, SILU>(a, s); break;
-  }
+template <int R>
+void launch_skinny(const GemmArgs& a, hipStream_t s) {
+  const int n_chunks = a.K / 128;
+  const int cps = (n_chunks + a.splits - 1) / a.splits;
+  launch_kernel((k_gemm_skinny<R, 1, false>), dim3(a.N / (64 * R), a.splits), dim3(256), 0, s, a, cps);
 }
 
 constexpr int kMaxSplitsAny = 64;
 
-enum GemmKernel { kKStream = 1, kKSkinny16 = 2, kKSkinny32 = 3, kKTiled = 4, kKF32 = 5, kKDeep = 6 };
+enum GemmKernel { kKStream = 1, kKSkinny16 = 2, kKSkinny32 = 3, kKTiled = 4, kKF32 = 5, kKDeep = 6, kKRing = 7 };
 
 struct GemmPlan {
   int kernel;
   int splits;
-  int R = 0, D = 0;  // k_gemm_deep: weight fragments per block and register stages
+  int R = 0, D = 0;  // k_gemm_deep, k_gemm_ring: weight fragments per block; k_gemm_deep: register stages
   int bm = 256;      // k_gemm_tiled: activation rows per block tile
   int bn = 256;      // k_gemm_tiled: weight rows per block tile
 };
 
-template <int R, int MT, int D, bool SILU>
+template <int R, int D, bool SILU>
 void launch_deep_t(const GemmArgs& a, hipStream_t s) {
   const int KU = a.K / 64;
   const int ups = (KU + a.splits - 1) / a.splits;
   const int per = SILU ? R / 2 : R;
   const int nb = (a.N / 16 + per - 1) / per;
   if (a.Wp.n_seg > 0)
-    launch_kernel((k_gemm_deep<R, MT, D, SILU, true>), dim3(nb, a.splits), dim3(256), 0, s, a, ups);
+    launch_kernel((k_gemm_deep<R, 1, D, SILU, true>), dim3(nb, a.splits), dim3(256), 0, s, a, ups);
   else
-    launch_kernel((k_gemm_deep<R, MT, D, SILU, false>), dim3(nb, a.splits), dim3(256), 0, s, a, ups);
+    launch_kernel((k_gemm_deep<R, 1, D, SILU, false>), dim3(nb, a.splits), dim3(256), 0, s, a, ups);
+}
+
+template <int R, int MT, bool SILU>
+void launch_ring_t(const GemmArgs& a, hipStream_t s) {
+  const int KU = a.K / 64;
+  const int ups = (KU + a.splits - 1) / a.splits;
+  const int per = SILU ? R / 2 : R;
+  const int nb = (a.N / 16 + per - 1) / per;
+  if (a.Wp.n_seg > 0)
+    launch_kernel((k_gemm_ring<R, MT, SILU, true>), dim3(nb, a.splits), dim3(256), 0, s, a, ups);
+  else
+    launch_kernel((k_gemm_ring<R, MT, SILU, false>), dim3(nb, a.splits), dim3(256), 0, s, a, ups);
+}
+
+template <bool SILU>
+bool launch_ring(const GemmArgs& a, int R, hipStream_t s) {
+#define RP_RING(R_)                                           \
+  if (R == R_) {                                              \
+    switch ((a.M + 15) / 16) {                                \
+      case 1: launch_ring_t<R_, 1, SILU>(a, s); return true;  \
+      case 2: launch_ring_t<R_, 2, SILU>(a, s); return true;  \
+      case 3: launch_ring_t<R_, 3, SILU>(a, s); return true;  \
+      case 4: launch_ring_t<R_, 4, SILU>(a, s); return true;  \
+      default: return false;                                  \
+    }                                                         \
+  }
+  RP_RING(2) RP_RING(4) RP_RING(6) RP_RING(8) RP_RING(10)
+#undef RP_RING
+  return false;
 }
 
 // One thread per 16-byte piece of the packed matrix (the layout of launch_pack_weights).
@@ -898,25 +1087,17 @@ __global__ void k_pack_weights(const uint4* __restrict__ w, uint4* __restrict__ 
   }
 }
 
-// The (R, D) pairs instantiated for each activation tile count MT = ceil(M / 16).
+// The (R, D) pairs of k_gemm_deep.
 struct DeepCfg { int R, D; };
-constexpr DeepCfg kDeepCfg[4][4] = {
-    {{10, 2}, {8, 2}, {4, 4}, {0, 0}},
-    {{10, 2}, {8, 2}, {4, 4}, {0, 0}},
-    {{10, 2}, {8, 2}, {6, 2}, {0, 0}},
-    {{10, 2}, {8, 2}, {6, 2}, {4, 3}},
+constexpr DeepCfg kDeepCfg[] = {
+    {10, 2}, {8, 2}, {4, 4},
 };
 
 template <bool SILU>
 bool launch_deep(const GemmArgs& a, int R, int D, hipStream_t s) {
-#define RP_DEEP(MT_, R_, D_) \
-  if (mt == MT_ && R == R_ && D == D_) { launch_deep_t<R_, MT_, D_, SILU>(a, s); return true; }
-  const int mt = (a.M + 15) / 16;
-  RP_DEEP(1, 10, 2) RP_DEEP(1, 8, 2) RP_DEEP(1, 4, 4)
-  RP_DEEP(2, 10, 2) RP_DEEP(2, 8, 2) RP_DEEP(2, 4, 4)
-  RP_DEEP(3, 10, 2) RP_DEEP(3, 8, 2) RP_DEEP(3, 6, 2)
-  RP_DEEP(4, 10, 2) RP_DEEP(4, 8, 2) RP_DEEP(4, 6, 2) RP_DEEP(4, 4, 3)
-#undef RP_DEEP
+  if (R == 10 && D == 2) { launch_deep_t<10, 2, SILU>(a, s); return true; }
+  if (R == 8 && D == 2) { launch_deep_t<8, 2, SILU>(a, s); return true; }
+  if (R == 4 && D == 4) { launch_deep_t<4, 4, SILU>(a, s); return true; }
   return false;
 }
 
@@ -936,12 +1117,11 @@ int even_splits(int n_units, int want) {
 // breaks ties toward more weight rows per block.  Measured on the Qwen2.5
 // 7B decode shapes, this picks the best swept configuration or one within
 // a few percent of it.
-GemmPlan plan_deep(int M, int N, int K, bool silu, int max_splits) {
-  const int mt = (M + 15) / 16, KU = K / 64, units = N / 16;
+GemmPlan plan_deep(int N, int K, bool silu, int max_splits) {
+  const int KU = K / 64, units = N / 16;
   GemmPlan best{kKDeep, 1};
   double best_cost = 1e300;
-  for (const DeepCfg& c : kDeepCfg[mt - 1]) {
-    if (c.R == 0) continue;
+  for (const DeepCfg& c : kDeepCfg) {
     const int per = silu ? c.R / 2 : c.R;
     const int nb = (units + per - 1) / per;
     int S = 1;
@@ -951,10 +1131,38 @@ GemmPlan plan_deep(int M, int N, int K, bool silu, int max_splits) {
       S = even_splits(KU, S);
     }
     const int rounds = (nb * S + 255) / 256;
-    const double cost = static_cast<double>(rounds) * c.R * 16 * ((KU + S - 1) / S) * (1.0 + 0.15 * mt / c.R);
+    const double cost = static_cast<double>(rounds) * c.R * 16 * ((KU + S - 1) / S) * (1.0 + 0.15 / c.R);
     if (cost < best_cost) {
       best_cost = cost;
       best = GemmPlan{kKDeep, S, c.R, c.D};
+    }
+  }
+  return best;
+}
+
+// k_gemm_ring plan: fragments per block and K split, priced as rounds of 256 blocks (a block's rings
+// fill a CU's LDS) x (a start, the units of a wave with their fragments and activation tiles, and the
+// reduction) plus the fp32 partials the split writes and its consumer reads.  Fitted to a sweep of all R
+// and splits 1-16 at 1-64 rows of the 7B, 0.5B and 32B projections and heads: 0.7% from the fastest in
+// the geometric mean, at most 6%.
+GemmPlan plan_ring(int M, int N, int K, bool silu, int max_splits, bool* one_round = nullptr) {
+  const int KU = K / 64, units = N / 16, mt = (M + 15) / 16;
+  GemmPlan best{kKRing, 1};
+  double best_cost = 1e300;
+  for (int R : {2, 4, 6, 8, 10}) {
+    const int per = silu ? R / 2 : R;
+    const int nb = (units + per - 1) / per;
+    const int s_max = silu ? 1 : std::max(1, std::min(std::min(16, max_splits), KU / 4));
+    for (int S = 1; S <= s_max; ++S) {
+      if (even_splits(KU, S) != S) continue;
+      const int rounds = (nb * S + 255) / 256, wave_units = ((KU + S - 1) / S + 3) / 4;
+      const double cost = rounds * (8.0 + wave_units * (0.011 * R + 0.028 * mt) + 0.08 * R * mt) +
+                          (silu ? 0.0 : S * static_cast<double>(M) * N / 2.1e7);
+      if (cost < best_cost) {
+        best_cost = cost;
+        best = GemmPlan{kKRing, S, R};
+        if (one_round) *one_round = rounds == 1;
+      }
     }
   }
   return best;
@@ -999,15 +1207,28 @@ GemmPlan plan_tiled(int M, int N, int K, bool silu, int split_lo, int split_hi) 
 
 // Kernel and split choice, from sweeps of the Qwen2.5 decode shapes on
 // gfx950 (weights cycled through more than the 256 MB last-level cache so
-// that none is reused between launches): the deep-pipelined kernel for
-// decode batches of the weight matrices of 7B and larger models; the older
-// streaming kernels for the small matrices (the 0.5B model, the 7B output
-// projection at <= 16 rows), where launch latency dominates.
+// that none is reused between launches):
+//  * 17-64 rows: the LDS-ring kernel throughout.  At 64 rows gate/up of the 7B
+//    takes 47.6 against 61.9 us for the register ring, the 0.5B head 78.7
+//    against 111 us, the 0.5B q/k/v and o 5.2 against 9.8 us for the streaming
+//    kernels; at 17-32 rows the gains are 0-10% at 7B and 40% at 0.5B.
+//  * up to 16 rows: the ring for products of 60M weights and more that one
+//    round of blocks covers (7B gate/up 45.0 against 45.8 us, 32B down 44.1
+//    against 46.2), and for a small model's gate/up from 9 rows (7.1 against 8.2);
+//    the register ring from 14M weights (it runs several blocks per CU: the
+//    0.5B head takes 44 against 52 us; 7B q/k/v 8.7 against 9.4); the
+//    streaming kernels for smaller matrices, where launch latency dominates.
 GemmPlan plan_gemm(int bf16, int M, int N, int K, bool silu, int max_splits) {
   if (!bf16) return {kKF32, 1};
   if (M > 64) return plan_tiled(M, N, K, silu, 1, silu ? 1 : std::max(1, std::min(std::min(16, max_splits), K / kGBK / 2)));
   const double work = static_cast<double>(N) * K * (silu ? 2 : 1);
-  if (K % 64 == 0 && N % 16 == 0 && work >= (M > 16 ? 8.0e6 : 1.4e7)) return plan_deep(M, N, K, silu, max_splits);
+  const bool units = K % 64 == 0 && N % 16 == 0;
+  if (units && (M > 16 || work >= 6.0e7 || (silu && M > 8))) {
+    bool one_round = false;
+    const GemmPlan ring = plan_ring(M, N, K, silu, max_splits, &one_round);
+    if (M > 16 || one_round || work < 1.4e7) return ring;
+  }
+  if (units && work >= 1.4e7) return plan_deep(N, K, silu, max_splits);
   const int n_chunks = K / 128;
   auto pick = [&](int blocks, int target) {
     int s = 1;
@@ -1019,11 +1240,8 @@ GemmPlan plan_gemm(int bf16, int M, int N, int K, bool silu, int max_splits) {
     return even_splits(n_chunks, s);
   };
   if (silu) return {kKStream, 1};
-  if (M <= 16) {
-    if (N >= 16384) return {M <= 8 ? kKStream : kKSkinny32, 1};
-    return {kKSkinny16, pick(N / 64, 512)};
-  }
-  return {kKSkinny32, pick(N / 128, K >= 8192 ? 448 : 256)};
+  if (N >= 16384) return {M <= 8 ? kKStream : kKSkinny32, 1};
+  return {kKSkinny16, pick(N / 64, 512)};
 }
 
 }  // namespace
@@ -1045,17 +1263,16 @@ hipError_t launch_gemm(int bf16, const GemmArgs& a, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
   const bool silu = a.epi == kEpiSiluMul;
   if (a.splits < 1 || (silu && a.splits != 1)) return hipErrorInvalidValue;
-  GemmPlan plan{kKTiled, a.splits};  // more than 64 bf16 rows: the tile is chosen below, for the caller's split
-  if (!bf16 || a.M <= 64) plan = plan_gemm(bf16, a.M, a.N, a.K, silu, kMaxSplitsAny);
-  if (a.variant == kKDeep && plan.kernel != kKDeep && a.M <= 64) plan = plan_deep(a.M, a.N, a.K, silu, kMaxSplitsAny);
-  const int kernel = a.variant ? a.variant : plan.kernel;
+  // more than 64 bf16 rows: the tile is chosen below, for the caller's split
+  const GemmPlan plan = bf16 && a.M > 64 ? GemmPlan{kKTiled, a.splits} : plan_gemm(bf16, a.M, a.N, a.K, silu, kMaxSplitsAny);
+  const int kernel = plan.kernel;
   if (!bf16 || kernel == kKF32) {
     if (bf16 || a.splits != 1) return hipErrorInvalidValue;
     if (silu) launch_f32<true>(a, s);
     else launch_f32<false>(a, s);
     return hipGetLastError();
   }
-  if (kernel == kKTiled || a.M > 64) {
+  if (kernel == kKTiled) {
     if (a.K % kGBK != 0 || (silu && a.N % 128 != 0) || (!silu && a.N % 8 != 0)) return hipErrorInvalidValue;
     // 32-bit buffer offsets; every weight segment but the last a whole number of 16-row blocks
     if (static_cast<int64_t>(a.M + 256) * a.lda * 2 >= (int64_t{1} << 31)) return hipErrorInvalidValue;
@@ -1080,8 +1297,14 @@ hipError_t launch_gemm(int bf16, const GemmArgs& a, hipStream_t s) {
 #undef RP_TILED
     return hipGetLastError();
   }
+  if (kernel == kKRing) {
+    // 32-bit buffer offsets of the rings' copies: activations and one fragment's 16 weight rows
+    if (static_cast<int64_t>(a.M) * a.lda * 2 >= (int64_t{1} << 30) || static_cast<int64_t>(a.K) * 32 >= (int64_t{1} << 30))
+      return hipErrorInvalidValue;
+    const bool ok = silu ? launch_ring<true>(a, plan.R, s) : launch_ring<false>(a, plan.R, s);
+    return ok ? hipGetLastError() : hipErrorInvalidValue;
+  }
   if (kernel == kKDeep) {
-    if (a.K % 64 != 0 || a.N % 16 != 0 || plan.kernel != kKDeep) return hipErrorInvalidValue;
     const bool ok = silu ? launch_deep<true>(a, plan.R, plan.D, s) : launch_deep<false>(a, plan.R, plan.D, s);
     return ok ? hipGetLastError() : hipErrorInvalidValue;
   }
@@ -1089,18 +1312,16 @@ hipError_t launch_gemm(int bf16, const GemmArgs& a, hipStream_t s) {
   switch (kernel) {
     case kKStream:
       if (a.N % (silu ? 16 : 32) != 0) return hipErrorInvalidValue;
-      if (silu) launch_stream_m<true>(a, s);
-      else launch_stream_m<false>(a, s);
+      if (silu) launch_stream<true>(a, s);
+      else launch_stream<false>(a, s);
       break;
     case kKSkinny16:
       if (a.N % 64 != 0) return hipErrorInvalidValue;
-      if (silu) launch_skinny_m<2, true>(a, s);
-      else launch_skinny_m<1, false>(a, s);
+      launch_skinny<1>(a, s);
       break;
     case kKSkinny32:
-      if (a.N % (silu ? 64 : 128) != 0) return hipErrorInvalidValue;
-      if (silu) launch_skinny_m<2, true>(a, s);
-      else launch_skinny_m<2, false>(a, s);
+      if (a.N % 128 != 0) return hipErrorInvalidValue;
+      launch_skinny<2>(a, s);
       break;
     default:
       return hipErrorInvalidValue;

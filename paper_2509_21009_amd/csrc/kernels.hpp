@@ -72,12 +72,11 @@ struct GemmArgs {
   int M, N, K;       // N: output columns (for kEpiSiluMul: I, with W = {gate, up})
   WSeg W;
   WSeg Wp;           // the same segments in the packed layout of launch_pack_weights (n_seg 0: none);
-                     // the decode-regime deep kernel reads them when present
+                     // the decode-regime deep and ring kernels read them when present
   int epi;
   int splits;        // S >= 1; kEpiSiluMul requires 1
   float* part;       // [S, M, N] (kEpiPartial)
   void* act_out;     // [M, N] dtype T (kEpiSiluMul)
-  int variant;       // 0: automatic; 1 stream, 2/3 skinny (16/32 rows per wave), 4 tiled, 6 deep
 };
 
 // Packed weight layout for the decode GEMM (bf16, rows % 16 == 0, K % 64 == 0):

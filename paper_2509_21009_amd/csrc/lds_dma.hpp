@@ -20,6 +20,10 @@ __device__ __forceinline__ u32x4_raw raw_rsrc(const void* p, uint32_t bytes) {
 __device__ __forceinline__ void dma16(u32x4_raw r, uint32_t lds, int voff) {
   asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" : : "s"(lds), "v"(voff), "s"(r) : "memory", "m0");
 }
+// The same, marked non-temporal: for data that is read once and should not displace reused lines.
+__device__ __forceinline__ void dma16_nt(u32x4_raw r, uint32_t lds, int voff) {
+  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds" : : "s"(lds), "v"(voff), "s"(r) : "memory", "m0");
+}
 // s_waitcnt vmcnt(N), the other counters at their maxima (gfx9 encoding).
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {

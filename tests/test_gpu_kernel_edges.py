@@ -32,14 +32,14 @@ def _workload(shape, plens, seed):
                     np.ones(n, np.int32), np.arange(n, dtype=np.int32), 1.0, 11)
 
 
-def _parity(shape, plens, n_new, max_prefill, tol=2e-2, check=None):
+def _parity(shape, plens, n_new, max_prefill, tol=2e-2, check=None, pack=True):
     wd = make_weights(shape, seed=3, device=DEV)
     w64 = weights_to_numpy(wd)
     wl = _workload(shape, plens, len(plens) + sum(plens))
     ctx = max(plens) + n_new
     R = rp()
     eng = R.Engine(shape, R.weights_for_engine(wd), max_seqs=len(plens), max_prefill_tokens=max_prefill,
-                   max_context=ctx, kv_pages=sum((p + n_new + 63) // 64 for p in plens))
+                   max_context=ctx, kv_pages=sum((p + n_new + 63) // 64 for p in plens), pack_weights=pack)
     r = teacher_forced_parity(eng, shape, w64, wl, n_new, tol, 1.0, 11, check=check)
     eng.close()
     assert r.max_rel_err <= tol and r.id_mismatch == 0, r
@@ -85,3 +85,20 @@ def test_decode_attention_edges(n_q, n_kv, hd, plens):
     if (n_q + 2 * n_kv) * hd % 128 or n_q * hd % 128:
         shape = dataclasses.replace(shape, n_q=n_q, head_dim=128)
     _parity(shape, plens, 3, max_prefill=4096)
+
+
+@pytest.mark.parametrize("rows", [1, 8, 9, 16, 17, 31, 32, 33, 48, 49, 63, 64])
+@pytest.mark.parametrize("pack", [True, False])
+def test_decode_gemm_row_edges(rows, pack):
+    """Decode batches around the 16-row activation tiles of the ring GEMM and its 9- and 17-row rules,
+    packed and row-major weights.  Six and ten K units leave waves with one, two or three units, 640
+    and 1,152 weight rows ragged last blocks."""
+    _parity(SMALL, [1 + i % 5 for i in range(rows)], 3, max_prefill=1024, pack=pack)
+
+
+@pytest.mark.parametrize("rows,pack", [(3, True), (3, False), (16, True), (40, False), (64, True)])
+def test_decode_gemm_wide(rows, pack):
+    """The 7B layer's K = 3,584 and 18,944 (fourteen and dozens of units per wave, K splits, the ring at few
+    rows) and a ragged head of 8,320 rows."""
+    shape = ModelShape("wide", 1, 3584, 28, 4, 128, 18944, 8320, False, "bf16")
+    _parity(shape, [1 + i % 3 for i in range(rows)], 2, max_prefill=1024, pack=pack, check=[0, rows // 2, rows - 1])
