@@ -33,7 +33,6 @@
 // The SiLU epilogue pairs gate row i with up row i in one thread and writes
 // silu(gate) * up once, rounded to the storage type.
 #include <algorithm>
-#include <type_traits>
 
 #include "device_common.hpp"
 #include "kernels.hpp"
@@ -870,31 +869,34 @@ __global__ __launch_bounds__((64 * TiledCfg<BM, BN>::WAVES)) void k_gemm_tiled(G
   }
   wait_vmcnt<0>();  // no copy may land in this block's LDS after it ends
 
-  // acc register e of tile (ah, mt): m = ah BM/2 + (wm MT + mt) 32 + 8 (e/4) + 4 lh + e%4, n = bh BN/2 + wn 32 + l32
-  const int m0 = mb * BM + wm * MT * 32 + 4 * lh;
-  const int n0 = SILU ? nb * (BN / 2) + wn * 32 + l32 : nb * BN + wn * 32 + l32;
-  auto store = [&](auto full) {
+  // acc register e of tile (ah, mt): m = ah BM/2 + (wm MT + mt) 32 + 8 (e/4) + 4 lh + e%4, n = bh BN/2 + wn 32 + l32.
+  // Stores go through a resource over the tile's rows, which drops rows past M; columns past N start
+  // out of range.  (A branch per element doubled the kernel's code: 2-3 us of instruction fetch a launch.)
+  constexpr int ESZ = SILU ? 2 : 4, kOut = static_cast<int>(0x80000000u);
+  const int rows = min(BM, a.M - mb * BM);
+  char* out = SILU ? static_cast<char*>(a.act_out) : reinterpret_cast<char*>(a.part + static_cast<size_t>(split) * a.M * a.N);
+  const __amdgpu_buffer_rsrc_t ors = buffer_rsrc(out + static_cast<size_t>(mb) * BM * a.N * ESZ, static_cast<uint32_t>(rows) * a.N * ESZ);
+  int voff[2];
 #pragma unroll
-    for (int ah = 0; ah < 2; ++ah)
+  for (int bh = 0; bh < (SILU ? 1 : 2); ++bh) {
+    const int n = SILU ? nb * (BN / 2) + wn * 32 + l32 : nb * BN + bh * (BN / 2) + wn * 32 + l32;
+    voff[bh] = n < a.N ? ((wm * MT * 32 + 4 * lh) * a.N + n) * ESZ : kOut;
+  }
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
+  for (int ah = 0; ah < 2; ++ah)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int dm = ah * (BM / 2) + mt * 32 + 8 * (e >> 2) + (e & 3);
-          if (!full.value && m0 + dm >= a.M) continue;
-          if (SILU) {
-            bf16_t* out = static_cast<bf16_t*>(a.act_out) + static_cast<size_t>(m0) * a.N + n0;
-            out[static_cast<size_t>(dm) * a.N] = bf16_of(silu_fast(acc[ah][0][mt][e]) * acc[ah][1][mt][e]);
-          } else {
-            float* out = a.part + (static_cast<size_t>(split) * a.M + m0) * a.N + n0;
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int bh = 0; bh < 2; ++bh)
-              if (full.value || n0 + bh * (BN / 2) < a.N) out[static_cast<size_t>(dm) * a.N + bh * (BN / 2)] = acc[ah][bh][mt][e];
-          }
+      for (int e = 0; e < 16; ++e) {
+        const int row = (ah * (BM / 2) + mt * 32 + 8 * (e >> 2) + (e & 3)) * a.N * ESZ;
+        if (SILU) {
+          __builtin_amdgcn_raw_buffer_store_b16(bf16_of(silu_fast(acc[ah][0][mt][e]) * acc[ah][1][mt][e]), ors, voff[0] + row, 0, 0);
+        } else {
+#pragma unroll
+          for (int bh = 0; bh < 2; ++bh)
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[ah][bh][mt][e]), ors, voff[bh] + row, 0, 0);
         }
-  };
-  if ((mb + 1) * BM <= a.M && (SILU || (nb + 1) * BN <= a.N)) store(std::true_type{});
-  else store(std::false_type{});
+      }
 }
 
 // ---- fp32 model ------------------------------------------------------------
