@@ -708,7 +708,7 @@ struct TiledCfg {
 };
 
 template <int BM, int BN, bool SILU>
-__global__ __launch_bounds__((64 * TiledCfg<BM, BN>::WAVES)) void k_gemm_tiled(GemmArgs a, int kblocks_per_split, int n_mb, int n_nb, int gm) {
+__global__ __launch_bounds__((64 * TiledCfg<BM, BN>::WAVES)) void k_gemm_tiled(GemmArgs a, int kblocks_per_split, int n_mb, int n_nb, int nb0, int gm) {
   using C = TiledCfg<BM, BN>;
   constexpr int MT = C::MT, NST = C::NST, LA = C::LA, LB = C::LB, WAVES = C::WAVES;
   constexpr int ROWB = kGBK * 2;                                   // bytes of an LDS row
@@ -728,7 +728,7 @@ __global__ __launch_bounds__((64 * TiledCfg<BM, BN>::WAVES)) void k_gemm_tiled(G
   const int split = q / n_tiles, t = q - split * n_tiles;
   // Grouped order: consecutive tiles walk gm m tiles of one weight panel, then the next panel.
   const int gsz = gm * n_nb, grp = t / gsz, first = grp * gm, gcur = min(gm, n_mb - first);
-  const int mb = first + (t - grp * gsz) % gcur, nb = (t - grp * gsz) / gcur;
+  const int mb = first + (t - grp * gsz) % gcur, nb = nb0 + (t - grp * gsz) / gcur;  // panels nb0 .. nb0 + n_nb - 1
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave % C::WM, wn = wave / C::WM;
@@ -1034,6 +1034,8 @@ struct GemmPlan {
   int R = 0, D = 0;  // k_gemm_deep, k_gemm_ring: weight fragments per block; k_gemm_deep: register stages
   int bm = 256;      // k_gemm_tiled: activation rows per block tile
   int bn = 256;      // k_gemm_tiled: weight rows per block tile
+  int n_first = 0;   // k_gemm_tiled: columns of the first launch; the rest run in bm2 x bn2 tiles
+  int bm2 = 256, bn2 = 256;
 };
 
 template <int R, int D, bool SILU>
@@ -1178,33 +1180,71 @@ GemmPlan plan_ring(int M, int N, int K, bool silu, int max_splits, bool* one_rou
 // round has no more than one block per CU.  Fitted to a sweep of all tile shapes
 // and splits 1-16 at 70-9,216 rows of the 7B, 0.5B and 32B projections: the
 // plans are 1.0% from the fastest in the geometric mean and at most 8%.
+// An unsplit product may run as two launches: the columns that fill whole rounds
+// of 256 x 256 tiles, and the rest in the tile that is fastest for them, instead
+// of a nearly empty last round (7B gate/up at 257-512 rows is 296 tiles on 256
+// CUs: 128 against 154 us at 397 rows, 136 against 163 at 512; 0.5B gate/up at 2,000
+// rows 42.6 against 49.1).
+struct Tile { int bm, bn; double ends, step; };
+constexpr Tile kTiles[] = {{256, 256, 1.5, 1.09}, {256, 128, 5.5, 0.654}, {128, 256, 5.5, 0.654}, {128, 128, 1.0, 0.955}};
+constexpr double kSecondLaunchUs = 2.5;
+
+// Weight rows of a tile panel are bn, of which a SiLU product makes bn / 2 outputs.
+int panels(int n, int bn, bool silu) { return silu ? (2 * n + bn - 1) / bn : (n + bn - 1) / bn; }
+
+double tile_cost(const Tile& c, int M, int N, bool silu, int splits, int steps) {
+  const int items = panels(N, c.bn, silu) * ((M + c.bm - 1) / c.bm) * splits;
+  if (c.bm != 128 || c.bn != 128) return (items + 255) / 256 * (c.ends + steps * c.step);
+  const int rem = items % 512;
+  double cost = (items / 512) * (c.ends + steps * c.step);
+  if (rem) cost += c.ends + steps * (rem <= 256 ? 0.556 : c.step);
+  return cost;
+}
+
 GemmPlan plan_tiled(int M, int N, int K, bool silu, int split_lo, int split_hi) {
   const int KB = K / kGBK;
   GemmPlan best{kKTiled, 1};
   double best_cost = 1e300;
-  struct Tile { int bm, bn; double ends, step; };
-  for (const Tile& c : {Tile{256, 256, 1.5, 1.09}, Tile{256, 128, 5.5, 0.654}, Tile{128, 256, 5.5, 0.654},
-                        Tile{128, 128, 1.0, 0.955}}) {
-    const int n_tiles = (silu ? N / (c.bn / 2) : (N + c.bn - 1) / c.bn) * ((M + c.bm - 1) / c.bm);
-    for (int sp = split_lo; sp <= split_hi; ++sp) {
-      if (split_hi > split_lo && even_splits(KB, sp) != sp) continue;
-      const int items = n_tiles * sp, per = (KB + sp - 1) / sp;
-      double cost;
-      if (c.bm == 128 && c.bn == 128) {
-        const int rem = items % 512;
-        cost = (items / 512) * (c.ends + per * c.step);
-        if (rem) cost += c.ends + per * (rem <= 256 ? 0.556 : c.step);
-      } else {
-        cost = (items + 255) / 256 * (c.ends + per * c.step);
-      }
-      if (!silu) cost += sp * static_cast<double>(M) * N * 8 / 4.2e6;
-      if (cost < best_cost) {
-        best_cost = cost;
-        best = GemmPlan{kKTiled, sp, 0, 0, c.bm, c.bn};
-      }
+  for (int sp = split_lo; sp <= split_hi; ++sp) {
+    if (split_hi > split_lo && even_splits(KB, sp) != sp) continue;
+    const int steps = (KB + sp - 1) / sp;
+    const double part = silu ? 0.0 : sp * static_cast<double>(M) * N * 8 / 4.2e6;
+    auto take = [&](double cost, int bm, int bn, int n_first, const Tile& rest) {
+      if (cost + part >= best_cost) return;
+      best_cost = cost + part;
+      best = GemmPlan{kKTiled, sp, 0, 0, bm, bn, n_first, rest.bm, rest.bn};
+    };
+    for (const Tile& c : kTiles) take(tile_cost(c, M, N, silu, sp, steps), c.bm, c.bn, N, c);
+    const Tile& big = kTiles[0];
+    const int n_mb = (M + big.bm - 1) / big.bm, tiles = n_mb * panels(N, big.bn, silu);
+    if (sp == 1 && tiles > 256) {
+      const int n_first = 256 * (tiles / 256) / n_mb * (silu ? big.bn / 2 : big.bn);  // whole panels of whole rounds
+      if (n_first > 0 && n_first < N)
+        for (const Tile& c : kTiles)
+          take(tile_cost(big, M, n_first, silu, 1, steps) + tile_cost(c, M, N - n_first, silu, 1, steps) + kSecondLaunchUs,
+               big.bm, big.bn, n_first, c);
     }
   }
   return best;
+}
+
+// Columns [n_lo, n_hi) of the product, n_lo at a panel's start.
+void launch_tiled(const GemmArgs& a, int bm, int bn, int n_lo, int n_hi, hipStream_t s) {
+  const bool silu = a.epi == kEpiSiluMul;
+  const int kbps = (a.K / kGBK + a.splits - 1) / a.splits;
+  const int n_nb = panels(n_hi - n_lo, bn, silu), nb0 = n_lo / (silu ? bn / 2 : bn);
+  const int n_mb = (a.M + bm - 1) / bm;
+  const int per_xcd = (n_mb * n_nb * a.splits + 7) / 8;
+  const int gm = n_nb >= 64 ? 8 : 2;
+  dim3 grid(8 * per_xcd);
+#define RP_TILED(BM_, BN_)                                                                                   \
+  if (bm == BM_ && bn == BN_) {                                                                              \
+    constexpr int threads = 64 * TiledCfg<BM_, BN_>::WAVES;                                                  \
+    if (silu) launch_kernel((k_gemm_tiled<BM_, BN_, true>), grid, dim3(threads), 0, s, a, kbps, n_mb, n_nb, nb0, gm); \
+    else launch_kernel((k_gemm_tiled<BM_, BN_, false>), grid, dim3(threads), 0, s, a, kbps, n_mb, n_nb, nb0, gm);     \
+  }
+  RP_TILED(128, 128) RP_TILED(128, 256) RP_TILED(256, 128) RP_TILED(256, 256)
+#undef RP_TILED
 }
 
 // Kernel and split choice, from sweeps of the Qwen2.5 decode shapes on
@@ -1282,21 +1322,9 @@ hipError_t launch_gemm(int bf16, const GemmArgs& a, hipStream_t s) {
       if (static_cast<int64_t>(a.W.rows[sg]) * a.K * 2 >= (int64_t{1} << 31)) return hipErrorInvalidValue;
       if (!silu && sg < a.W.n_seg - 1 && a.W.rows[sg] % 16 != 0) return hipErrorInvalidValue;
     }
-    const GemmPlan tp = plan_tiled(a.M, a.N, a.K, silu, a.splits, a.splits);  // the best tile for the caller's split
-    const int bm = tp.bm, bn = tp.bn;
-    const int kbps = (a.K / kGBK + a.splits - 1) / a.splits;
-    const int n_nb = silu ? a.N / (bn / 2) : (a.N + bn - 1) / bn;
-    const int n_mb = (a.M + bm - 1) / bm;
-    const int per_xcd = (n_mb * n_nb * a.splits + 7) / 8;
-    const int gm = n_nb >= 64 ? 8 : 2;
-    dim3 grid(8 * per_xcd);
-#define RP_TILED(BM_, BN_)                                                                                   \
-    if (bm == BM_ && bn == BN_) {                                                                            \
-      if (silu) launch_kernel((k_gemm_tiled<BM_, BN_, true>), grid, dim3((64 * TiledCfg<BM_, BN_>::WAVES)), 0, s, a, kbps, n_mb, n_nb, gm); \
-      else launch_kernel((k_gemm_tiled<BM_, BN_, false>), grid, dim3((64 * TiledCfg<BM_, BN_>::WAVES)), 0, s, a, kbps, n_mb, n_nb, gm); \
-    }
-    RP_TILED(128, 128) RP_TILED(128, 256) RP_TILED(256, 128) RP_TILED(256, 256)
-#undef RP_TILED
+    const GemmPlan tp = plan_tiled(a.M, a.N, a.K, silu, a.splits, a.splits);  // the best tiles for the caller's split
+    launch_tiled(a, tp.bm, tp.bn, 0, tp.n_first, s);
+    if (tp.n_first < a.N) launch_tiled(a, tp.bm2, tp.bn2, tp.n_first, a.N, s);
     return hipGetLastError();
   }
   if (kernel == kKRing) {

@@ -96,9 +96,9 @@ def test_decode_gemm_row_edges(rows, pack):
     _parity(SMALL, [1 + i % 5 for i in range(rows)], 3, max_prefill=1024, pack=pack)
 
 
-@pytest.mark.parametrize("rows,pack", [(3, True), (3, False), (16, True), (40, False), (64, True)])
+@pytest.mark.parametrize("rows,pack", [(3, True), (3, False), (16, True), (40, False), (64, True), (397, True)])
 def test_decode_gemm_wide(rows, pack):
     """The 7B layer's K = 3,584 and 18,944 (fourteen and dozens of units per wave, K splits, the ring at few
-    rows) and a ragged head of 8,320 rows."""
+    rows) and a ragged head of 8,320 rows; at 397 rows gate/up in two launches of different tiles."""
     shape = ModelShape("wide", 1, 3584, 28, 4, 128, 18944, 8320, False, "bf16")
     _parity(shape, [1 + i % 3 for i in range(rows)], 2, max_prefill=1024, pack=pack, check=[0, rows // 2, rows - 1])
