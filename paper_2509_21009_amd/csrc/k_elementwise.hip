@@ -48,10 +48,20 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
   return t;
 }
 
+// The norm gains of this thread's chunks, loaded with the row so that the reduction does not delay them.
+template <typename T>
+__device__ __forceinline__ void load_gains(const T* g, int H, float4 (&gv)[kRowChunks]) {
+#pragma unroll
+  for (int v = 0; v < kRowChunks; ++v) {
+    const int c = threadIdx.x + v * blockDim.x;
+    if (c < H / 4) gv[v] = Vec4<T>::load(g, 4 * c);
+  }
+}
+
 // x holds the row (kRowChunks float4 per thread); writes h = x * rsqrt(mean(x^2)+eps) * g.
 template <typename T>
-__device__ __forceinline__ void norm_store(const float4 (&xv)[kRowChunks], int H, float eps, const T* g, T* h,
-                                           float* red) {
+__device__ __forceinline__ void norm_store(const float4 (&xv)[kRowChunks], const float4 (&gv)[kRowChunks], int H, float eps,
+                                           T* h, float* red) {
   const int nc = H / 4;
   float ss = 0.f;
 #pragma unroll
@@ -65,9 +75,9 @@ __device__ __forceinline__ void norm_store(const float4 (&xv)[kRowChunks], int H
   for (int v = 0; v < kRowChunks; ++v) {
     const int c = threadIdx.x + v * blockDim.x;
     if (c < nc) {
-      const float4 gv = Vec4<T>::load(g, 4 * c);
       Vec4<T>::store(h, 4 * static_cast<size_t>(c),
-                     make_float4(xv[v].x * inv * gv.x, xv[v].y * inv * gv.y, xv[v].z * inv * gv.z, xv[v].w * inv * gv.w));
+                     make_float4(xv[v].x * inv * gv[v].x, xv[v].y * inv * gv[v].y, xv[v].z * inv * gv[v].z,
+                                 xv[v].w * inv * gv[v].w));
     }
   }
 }
@@ -76,6 +86,8 @@ template <typename T>
 __global__ __launch_bounds__(1024) void k_embed_norm(EmbedArgs a) {
   __shared__ float red[16];
   const int i = blockIdx.x;
+  float4 gv[kRowChunks];
+  load_gains(static_cast<const T*>(a.norm_g), a.H, gv);
   int tok = a.in_tok[i];
   if (tok < 0) tok = a.tokens_cur[a.row_slot[i]];
   const T* e = static_cast<const T*>(a.embed) + static_cast<size_t>(tok) * a.H;
@@ -90,8 +102,7 @@ __global__ __launch_bounds__(1024) void k_embed_norm(EmbedArgs a) {
       *reinterpret_cast<float4*>(x + 4 * c) = xv[v];
     }
   }
-  norm_store<T>(xv, a.H, a.eps, static_cast<const T*>(a.norm_g), static_cast<T*>(a.h) + static_cast<size_t>(i) * a.H,
-                red);
+  norm_store<T>(xv, gv, a.H, a.eps, static_cast<T*>(a.h) + static_cast<size_t>(i) * a.H, red);
 }
 
 template <typename T, int S>
@@ -102,7 +113,8 @@ __global__ __launch_bounds__(1024) void k_add_rmsnorm(AddNormArgs a) {
   const int nc = a.H / 4;
   const size_t plane = static_cast<size_t>(a.M) * a.H;
   float4 xv[kRowChunks];
-  float4 pv[S > 0 ? S : 1][kRowChunks];
+  float4 pv[S > 0 ? S : 1][kRowChunks], gv[kRowChunks];
+  load_gains(static_cast<const T*>(a.norm_g), a.H, gv);
 #pragma unroll
   for (int v = 0; v < kRowChunks; ++v) {
     const int c = threadIdx.x + v * blockDim.x;
@@ -126,13 +138,11 @@ __global__ __launch_bounds__(1024) void k_add_rmsnorm(AddNormArgs a) {
       }
     }
   }
-  norm_store<T>(xv, a.H, a.eps, static_cast<const T*>(a.norm_g), static_cast<T*>(a.h) + static_cast<size_t>(i) * a.H,
-                red);
+  norm_store<T>(xv, gv, a.H, a.eps, static_cast<T*>(a.h) + static_cast<size_t>(i) * a.H, red);
 }
 
-// One thread per rotated (q or k) pair or per v element; blockIdx.y strides
+// fp32 model: one thread per rotated (q or k) pair or per v element; blockIdx.y strides
 // the row's items so small batches still fill the GPU.
-template <typename T, int S>
 __global__ __launch_bounds__(256) void k_rope_append(RopeArgs a) {
   const int i = blockIdx.x;
   const int hd = a.hd, half = hd / 2;
@@ -141,7 +151,6 @@ __global__ __launch_bounds__(256) void k_rope_append(RopeArgs a) {
   const int n_pairs = (a.n_q + a.n_kv) * half;
   const int t = blockIdx.y * blockDim.x + threadIdx.x;
   if (t >= n_pairs + nk_el) return;
-  const size_t plane = static_cast<size_t>(a.M) * nqkv;
   const float* __restrict__ prow = a.part + static_cast<size_t>(i) * nqkv;
   const int pos = a.pos[i];
   const int slot = a.slot[i];
@@ -150,48 +159,110 @@ __global__ __launch_bounds__(256) void k_rope_append(RopeArgs a) {
   if (t < n_pairs) {
     const int head = t / half, d = t % half;
     const int n1 = head * hd + d, n2 = n1 + half;
-    float u1 = 0.f, u2 = 0.f;
-#pragma unroll
-    for (int s = 0; s < S; ++s) {
-      u1 += prow[s * plane + n1];
-      u2 += prow[s * plane + n2];
-    }
     const bool isq = head < a.n_q;
-    const T* b = isq ? static_cast<const T*>(a.bq) : static_cast<const T*>(a.bk);
+    const float* b = static_cast<const float*>(isq ? a.bq : a.bk);
     const int bi = isq ? n1 : n1 - nq_el;
-    u1 += Elem<T>::load(b, bi);
-    u2 += Elem<T>::load(b, bi + half);
+    const float u1 = prow[n1] + b[bi], u2 = prow[n2] + b[bi + half];
     const float c = a.rope_cos[static_cast<size_t>(pos) * half + d];
     const float sn = a.rope_sin[static_cast<size_t>(pos) * half + d];
-    const float r1 = u1 * c - u2 * sn;
-    const float r2 = u2 * c + u1 * sn;
-    if (head < a.n_q) {
-      T* q = static_cast<T*>(a.q_out) + static_cast<size_t>(i) * nq_el;
-      Elem<T>::store(q, n1, r1);
-      Elem<T>::store(q, n2, r2);
-    } else {
-      const int kh = head - a.n_q;
-      const size_t blk = (static_cast<size_t>(page) * a.n_kv + kh) * kPageTokens * hd;
-      if (sizeof(T) == 2) {  // bf16 cache: MFMA operand order
-        Elem<T>::store(static_cast<T*>(a.k_pool), blk + k_page_offset(off, d, hd), r1);
-        Elem<T>::store(static_cast<T*>(a.k_pool), blk + k_page_offset(off, d + half, hd), r2);
-      } else {
-        Elem<T>::store(static_cast<T*>(a.k_pool), blk + static_cast<size_t>(off) * hd + d, r1);
-        Elem<T>::store(static_cast<T*>(a.k_pool), blk + static_cast<size_t>(off) * hd + d + half, r2);
-      }
-    }
+    float* dst = isq ? static_cast<float*>(a.q_out) + static_cast<size_t>(i) * nq_el + n1
+                     : static_cast<float*>(a.k_pool) +
+                           ((static_cast<size_t>(page) * a.n_kv + head - a.n_q) * kPageTokens + off) * hd + d;
+    dst[0] = u1 * c - u2 * sn;
+    dst[half] = u2 * c + u1 * sn;
   } else {
     const int e = t - n_pairs;
     const int kh = e / hd, d = e % hd;
-    const int n = nq_el + nk_el + e;
-    float v = 0.f;
-#pragma unroll
-    for (int s = 0; s < S; ++s) v += prow[s * plane + n];
-    v += Elem<T>::load(static_cast<const T*>(a.bv), e);
     // V page: two 32-token halves, each [hd][32 tokens]
     const size_t idx = (static_cast<size_t>(page) * a.n_kv + kh) * hd * kPageTokens + (off >> 5) * hd * 32 + d * 32 + (off & 31);
-    Elem<T>::store(static_cast<T*>(a.v_pool), idx, v);
+    static_cast<float*>(a.v_pool)[idx] = prow[nq_el + nk_el + e] + static_cast<const float*>(a.bv)[e];
   }
+}
+
+// The bf16 prefill's bias, RoPE and append, 16 bytes of partials at a time.  The first blocks take the
+// q and k pairs, four consecutive dimension pairs per thread.  The rest take 64 tokens x 64 value
+// dimensions each and turn them through LDS: a V page holds a dimension's 32 tokens side by side, so
+// lanes store along tokens (64-byte runs) instead of 2 bytes per cache line.  ONE: a single partial.
+// 11,500 tokens of the 7B shape: 66 us (4.6 TB/s) against 140 for one pair or value per thread; 9,216 tokens of
+// the 0.5B 14.6 against 24.8 us.
+constexpr int kRopeTok = 64, kRopeDim = 64;
+
+template <bool ONE>
+__global__ __launch_bounds__(256) void k_rope_prefill(RopeArgs a, int qk_blocks_per_row) {
+  __shared__ bf16_t sv[kRopeDim][kRopeTok + 2];
+  const int hd = a.hd, half = hd / 2;
+  const int nq_el = a.n_q * hd, nk_el = a.n_kv * hd, nqkv = nq_el + 2 * nk_el;
+  const size_t plane = static_cast<size_t>(a.M) * nqkv;
+  const int S = ONE ? 1 : a.splits;
+  auto sum4 = [&](const float* p) {
+    float4 u = *reinterpret_cast<const float4*>(p);
+    if (!ONE) {
+#pragma unroll 4
+      for (int s = 1; s < S; ++s) {
+        const float4 w = *reinterpret_cast<const float4*>(p + s * plane);
+        u.x += w.x; u.y += w.y; u.z += w.z; u.w += w.w;
+      }
+    }
+    return u;
+  };
+  const int n_qk = a.M * qk_blocks_per_row;
+  if (static_cast<int>(blockIdx.x) < n_qk) {
+    const int i = blockIdx.x / qk_blocks_per_row;
+    const int t = (blockIdx.x - i * qk_blocks_per_row) * 256 + threadIdx.x;
+    const int per_head = half / 4;
+    if (t >= (a.n_q + a.n_kv) * per_head) return;
+    const int head = t / per_head, d = (t - head * per_head) * 4, n1 = head * hd + d;
+    const bool isq = head < a.n_q;
+    const int pos = a.pos[i];
+    const float* p = a.part + static_cast<size_t>(i) * nqkv + n1;
+    const bf16_t* b = static_cast<const bf16_t*>(isq ? a.bq : a.bk) + (isq ? n1 : n1 - nq_el);
+    float4 u1 = sum4(p), u2 = sum4(p + half);
+    float b1[4], b2[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      b1[e] = bf16_to_f32(b[e]);
+      b2[e] = bf16_to_f32(b[half + e]);
+    }
+    const float4 c = *reinterpret_cast<const float4*>(a.rope_cos + static_cast<size_t>(pos) * half + d);
+    const float4 sn = *reinterpret_cast<const float4*>(a.rope_sin + static_cast<size_t>(pos) * half + d);
+    u1.x += b1[0]; u1.y += b1[1]; u1.z += b1[2]; u1.w += b1[3];
+    u2.x += b2[0]; u2.y += b2[1]; u2.z += b2[2]; u2.w += b2[3];
+    const float4 r1 = make_float4(u1.x * c.x - u2.x * sn.x, u1.y * c.y - u2.y * sn.y, u1.z * c.z - u2.z * sn.z, u1.w * c.w - u2.w * sn.w);
+    const float4 r2 = make_float4(u2.x * c.x + u1.x * sn.x, u2.y * c.y + u1.y * sn.y, u2.z * c.z + u1.z * sn.z, u2.w * c.w + u1.w * sn.w);
+    if (isq) {
+      bf16_t* q = static_cast<bf16_t*>(a.q_out) + static_cast<size_t>(i) * nq_el;
+      Vec4<bf16_t>::store(q, n1, r1);
+      Vec4<bf16_t>::store(q, n1 + half, r2);
+    } else {
+      const int page = a.page_table[static_cast<size_t>(a.slot[i]) * a.pt_stride + pos / kPageTokens], off = pos % kPageTokens;
+      bf16_t* k = static_cast<bf16_t*>(a.k_pool) + (static_cast<size_t>(page) * a.n_kv + head - a.n_q) * kPageTokens * hd;
+      Vec4<bf16_t>::store(k, k_page_offset(off, d, hd), r1);  // four dimensions of an 8-dimension run
+      Vec4<bf16_t>::store(k, k_page_offset(off, d + half, hd), r2);
+    }
+    return;
+  }
+  const int vb = blockIdx.x - n_qk, d_blocks = nk_el / kRopeDim;
+  const int i0 = vb / d_blocks * kRopeTok, d0 = vb % d_blocks * kRopeDim;  // within one KV head: hd is a multiple of 64
+  const int dd = (threadIdx.x & 15) * 4;
+#pragma unroll
+  for (int j = 0; j < kRopeTok / 16; ++j) {
+    const int tok = (threadIdx.x >> 4) + 16 * j, i = i0 + tok;
+    if (i >= a.M) break;
+    const float4 u = sum4(a.part + static_cast<size_t>(i) * nqkv + nq_el + nk_el + d0 + dd);
+    const bf16_t* b = static_cast<const bf16_t*>(a.bv) + d0 + dd;
+    sv[dd + 0][tok] = f32_to_bf16(u.x + bf16_to_f32(b[0]));
+    sv[dd + 1][tok] = f32_to_bf16(u.y + bf16_to_f32(b[1]));
+    sv[dd + 2][tok] = f32_to_bf16(u.z + bf16_to_f32(b[2]));
+    sv[dd + 3][tok] = f32_to_bf16(u.w + bf16_to_f32(b[3]));
+  }
+  __syncthreads();
+  const int tok = threadIdx.x & 63, i = i0 + tok, w = threadIdx.x >> 6;
+  if (i >= a.M) return;
+  const int pos = a.pos[i], page = a.page_table[static_cast<size_t>(a.slot[i]) * a.pt_stride + pos / kPageTokens], off = pos % kPageTokens;
+  // V page: two 32-token halves, each [hd][32 tokens]
+  bf16_t* v = static_cast<bf16_t*>(a.v_pool) + (static_cast<size_t>(page) * a.n_kv + d0 / hd) * hd * kPageTokens + (off >> 5) * hd * 32 + (off & 31);
+#pragma unroll
+  for (int k = 0; k < kRopeDim / 4; ++k) v[(d0 % hd + w * (kRopeDim / 4) + k) * 32] = sv[w * (kRopeDim / 4) + k][tok];
 }
 
 // ---- sampling -------------------------------------------------------------
@@ -206,8 +277,10 @@ __device__ __forceinline__ void philox4x64_10(uint64_t& x0, uint64_t& x1, uint64
                                               uint64_t k0, uint64_t k1) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
-    const uint64_t hi0 = __umul64hi(kPhiloxM0, x0), lo0 = kPhiloxM0 * x0;
-    const uint64_t hi1 = __umul64hi(kPhiloxM1, x2), lo1 = kPhiloxM1 * x2;
+    const unsigned __int128 p0 = static_cast<unsigned __int128>(kPhiloxM0) * x0;  // four 32 x 32 products each
+    const unsigned __int128 p1 = static_cast<unsigned __int128>(kPhiloxM1) * x2;
+    const uint64_t hi0 = static_cast<uint64_t>(p0 >> 64), lo0 = static_cast<uint64_t>(p0);
+    const uint64_t hi1 = static_cast<uint64_t>(p1 >> 64), lo1 = static_cast<uint64_t>(p1);
     const uint64_t n0 = hi1 ^ x1 ^ k0, n2 = hi0 ^ x3 ^ k1;
     x0 = n0; x1 = lo1; x2 = n2; x3 = lo0;
     k0 += kPhiloxW0;
@@ -222,14 +295,13 @@ __device__ __forceinline__ float word_to_gumbel(uint32_t w) {
 }
 
 __device__ __forceinline__ void take_best(float& bv, int& bi, float v, int i) {
-  if (v > bv || (v == bv && i < bi)) { bv = v; bi = i; }
+  const bool take = (v > bv) | ((v == bv) & (i < bi));  // no branch; a NaN is never taken
+  bv = take ? v : bv;
+  bi = take ? i : bi;
 }
 
 // Running log-sum-exp state (max m, sum of exp(x - m)); combining two states
 // rescales the smaller-max sum.
-__device__ __forceinline__ void lse_add(float& m, float& s, float x) {
-  if (x > m) { s = s * expf(m - x) + 1.f; m = x; } else { s += expf(x - m); }
-}
 __device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2) {
   if (m2 == -INFINITY) return;
   if (m2 > m) { s = s * expf(m - m2) + s2; m = m2; } else { s += s2 * expf(m2 - m); }
@@ -246,41 +318,47 @@ __global__ __launch_bounds__(256) void k_sample_partial(SampleArgs a) {
   __shared__ float sv[4], sm[4], ss[4];
   __shared__ int si[4];
   const int row = blockIdx.x;
+  const float* l = a.logits + static_cast<size_t>(row) * a.V;
+  const int gi = blockIdx.y * (kSampleChunk / 8) + threadIdx.x;  // 8 entries per thread, one Philox block
+  const int vb = gi * 8;
+  float lv[8];
+  const bool whole = vb + 8 <= a.V && a.V % 4 == 0;  // then the entries are two 16-byte loads
+  if (whole) {
+    const float4 p = *reinterpret_cast<const float4*>(l + vb), q = *reinterpret_cast<const float4*>(l + vb + 4);
+    lv[0] = p.x; lv[1] = p.y; lv[2] = p.z; lv[3] = p.w;
+    lv[4] = q.x; lv[5] = q.y; lv[6] = q.z; lv[7] = q.w;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) lv[e] = vb + e < a.V ? l[vb + e] : -INFINITY;
+  }
   const int slot = a.row_slot[row];
   const float temp = a.slot_temp[slot];
-  const float* l = a.logits + static_cast<size_t>(row) * a.V;
   float best = -INFINITY;
   int besti = 0x7fffffff;
   float lm = -INFINITY, ls = 0.f;  // log-sum-exp state of logits / T
-  const int v0 = blockIdx.y * kSampleChunk;
-  if (temp == 0.f) {
+  if (vb < a.V) {
+    if (temp == 0.f) {
 #pragma unroll
-    for (int e = 0; e < kSampleChunk / 256; ++e) {
-      const int v = v0 + e * 256 + threadIdx.x;
-      if (v < a.V) {
-        take_best(best, besti, l[v], v);
-        lse_add(lm, ls, l[v]);
-      }
-    }
-  } else {
-    const float inv_t = 1.0f / temp;
-    const int gi = (v0 >> 3) + threadIdx.x;   // 8 entries per thread, one Philox block
-    const int vb = gi * 8;
-    if (vb < a.V) {
-      float lv[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) lv[e] = (vb + e < a.V) ? l[vb + e] : -INFINITY;
+      for (int e = 0; e < 8; ++e)
+        take_best(best, besti, vb + e < a.V ? lv[e] : NAN, vb + e);
+    } else {
+      const float inv_t = 1.0f / temp;
       uint64_t x0 = static_cast<uint64_t>(a.row_pos[row]), x1 = static_cast<uint64_t>(gi), x2 = 0, x3 = 0;
       philox4x64_10(x0, x1, x2, x3, a.slot_seed[slot], a.slot_id[slot]);
       const uint64_t outs[4] = {x0, x1, x2, x3};
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        if (vb + e < a.V) {
-          const uint32_t w = (e & 1) ? static_cast<uint32_t>(outs[e >> 1] >> 32) : static_cast<uint32_t>(outs[e >> 1]);
-          take_best(best, besti, lv[e] * inv_t + word_to_gumbel(w), vb + e);
-          lse_add(lm, ls, lv[e] * inv_t);
-        }
+        const uint32_t w = (e & 1) ? static_cast<uint32_t>(outs[e >> 1] >> 32) : static_cast<uint32_t>(outs[e >> 1]);
+        lv[e] *= inv_t;
+        take_best(best, besti, vb + e < a.V ? lv[e] + word_to_gumbel(w) : NAN, vb + e);
       }
+    }
+    // the thread's log-sum-exp around its own maximum (entries past V are -inf and add nothing)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) lm = fmaxf(lm, lv[e]);
+    if (lm > -INFINITY) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) ls += expf(lv[e] - lm);
     }
   }
 #pragma unroll
@@ -312,6 +390,8 @@ __global__ __launch_bounds__(256) void k_sample_partial(SampleArgs a) {
 
 __global__ __launch_bounds__(64) void k_sample_final(SampleArgs a, int chunks) {
   const int row = blockIdx.x;
+  const int slot = a.row_slot[row], hist = a.row_hist[row];
+  const float temp = a.slot_temp[slot];
   float best = -INFINITY;
   int besti = 0x7fffffff;
   float lm = -INFINITY, ls = 0.f;
@@ -331,11 +411,9 @@ __global__ __launch_bounds__(64) void k_sample_final(SampleArgs a, int chunks) {
   }
   if (threadIdx.x == 0) {
     if (besti == 0x7fffffff) besti = 0;  // all-NaN row: deterministic fallback
-    const int slot = a.row_slot[row];
-    const float temp = a.slot_temp[slot];
     const float inv_t = temp == 0.f ? 1.f : 1.0f / temp;
     const float s_tok = a.logits[static_cast<size_t>(row) * a.V + besti] * inv_t;
-    const size_t h = static_cast<size_t>(slot) * a.hist_stride + a.row_hist[row];
+    const size_t h = static_cast<size_t>(slot) * a.hist_stride + hist;
     a.tokens_cur[slot] = besti;
     a.hist[h] = besti;
     a.logp_hist[h] = s_tok - (lm + logf(ls));
@@ -396,29 +474,22 @@ hipError_t launch_add_norm_t(const AddNormArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_rope_t(const RopeArgs& a, hipStream_t s) {
+// fp32 model: one partial, no K split.
+hipError_t launch_rope_f32(const RopeArgs& a, hipStream_t s) {
+  if (a.splits != 1) return hipErrorInvalidValue;
   const int items = (a.n_q + a.n_kv) * (a.hd / 2) + a.n_kv * a.hd;
-  dim3 grid(a.M, (items + 255) / 256);
-  switch (a.splits) {
-    case 1: launch_kernel((k_rope_append<T, 1>), grid, dim3(256), 0, s, a); break;
-    case 2: launch_kernel((k_rope_append<T, 2>), grid, dim3(256), 0, s, a); break;
-    case 3: launch_kernel((k_rope_append<T, 3>), grid, dim3(256), 0, s, a); break;
-    case 4: launch_kernel((k_rope_append<T, 4>), grid, dim3(256), 0, s, a); break;
-    case 5: launch_kernel((k_rope_append<T, 5>), grid, dim3(256), 0, s, a); break;
-    case 6: launch_kernel((k_rope_append<T, 6>), grid, dim3(256), 0, s, a); break;
-    case 7: launch_kernel((k_rope_append<T, 7>), grid, dim3(256), 0, s, a); break;
-    case 8: launch_kernel((k_rope_append<T, 8>), grid, dim3(256), 0, s, a); break;
-    case 9: launch_kernel((k_rope_append<T, 9>), grid, dim3(256), 0, s, a); break;
-    case 10: launch_kernel((k_rope_append<T, 10>), grid, dim3(256), 0, s, a); break;
-    case 11: launch_kernel((k_rope_append<T, 11>), grid, dim3(256), 0, s, a); break;
-    case 12: launch_kernel((k_rope_append<T, 12>), grid, dim3(256), 0, s, a); break;
-    case 13: launch_kernel((k_rope_append<T, 13>), grid, dim3(256), 0, s, a); break;
-    case 14: launch_kernel((k_rope_append<T, 14>), grid, dim3(256), 0, s, a); break;
-    case 15: launch_kernel((k_rope_append<T, 15>), grid, dim3(256), 0, s, a); break;
-    case 16: launch_kernel((k_rope_append<T, 16>), grid, dim3(256), 0, s, a); break;
-    default: return hipErrorInvalidValue;
-  }
+  launch_kernel(k_rope_append, dim3(a.M, (items + 255) / 256), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+// bf16 prefill.  Partials, tables and pools are 256-byte aligned parts of the engine's workspaces.
+hipError_t launch_rope_bf16(const RopeArgs& a, hipStream_t s) {
+  if (a.hd % kRopeDim || a.splits < 1) return hipErrorInvalidValue;
+  const int per_row = ((a.n_q + a.n_kv) * (a.hd / 8) + 255) / 256;
+  const int v_blocks = (a.M + kRopeTok - 1) / kRopeTok * (a.n_kv * a.hd / kRopeDim);
+  const dim3 grid(a.M * per_row + v_blocks);
+  if (a.splits == 1) launch_kernel(k_rope_prefill<true>, grid, dim3(256), 0, s, a, per_row);
+  else launch_kernel(k_rope_prefill<false>, grid, dim3(256), 0, s, a, per_row);
   return hipGetLastError();
 }
 }  // namespace
@@ -440,7 +511,7 @@ hipError_t launch_add_rmsnorm(int bf16, const AddNormArgs& a, hipStream_t s) {
 
 hipError_t launch_rope_append(int bf16, const RopeArgs& a, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
-  return bf16 ? launch_rope_t<bf16_t>(a, s) : launch_rope_t<float>(a, s);
+  return bf16 ? launch_rope_bf16(a, s) : launch_rope_f32(a, s);
 }
 
 int sample_chunks(int V) { return (V + kSampleChunk - 1) / kSampleChunk; }
