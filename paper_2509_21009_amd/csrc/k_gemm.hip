@@ -33,6 +33,7 @@
 // The SiLU epilogue pairs gate row i with up row i in one thread and writes
 // silu(gate) * up once, rounded to the storage type.
 #include <algorithm>
+#include <cmath>
 
 #include "device_common.hpp"
 #include "kernels.hpp"
@@ -1031,11 +1032,11 @@ void launch_skinny(const GemmArgs& a, hipStream_t s) {
 
 constexpr int kMaxSplitsAny = 64;
 
-enum GemmKernel { kKStream = 1, kKSkinny16 = 2, kKSkinny32 = 3, kKTiled = 4, kKF32 = 5, kKDeep = 6, kKRing = 7 };
+enum GemmKernel { kKNone = 0, kKStream = 1, kKSkinny16 = 2, kKSkinny32 = 3, kKTiled = 4, kKF32 = 5, kKDeep = 6, kKRing = 7 };
 
 struct GemmPlan {
-  int kernel;
-  int splits;
+  int kernel = kKNone;
+  int splits = 1;
   int R = 0, D = 0;  // k_gemm_deep, k_gemm_ring: weight fragments per block; k_gemm_deep: register stages
   int bm = 256;      // k_gemm_tiled: activation rows per block tile
   int bn = 256;      // k_gemm_tiled: weight rows per block tile
@@ -1149,13 +1150,15 @@ GemmPlan plan_deep(int N, int K, bool silu, int max_splits) {
   return best;
 }
 
-// k_gemm_ring plan: fragments per block and K split, priced as rounds of 256 blocks (a block's rings
-// fill a CU's LDS) x (a start, the units of a wave with their fragments and activation tiles, and the
-// reduction) plus the fp32 partials the split writes and its consumer reads.  Fitted to a sweep of all R
-// and splits 1-16 at 1-64 rows of the 7B, 0.5B and 32B projections and heads: 0.7% from the fastest in
-// the geometric mean, at most 6%.
+// k_gemm_ring plan: fragments per block and K split, priced in us.  A launch takes what its fullest CU does
+// (rounds of 256 blocks, whose rings fill a CU's LDS: the units of a wave with their fragments and
+// activation tiles, the reduction) and what the weights take at the HBM rate, neither hiding quite behind the
+// other (root of the squares), plus the fp32 partials and a little per plane of them.  Fitted to a sweep of all R and splits 1-16 at
+// 1-64 rows of the 7B, 0.5B and 32B projections and heads: 0.5% from the fastest in the geometric mean, at
+// most 5%.
 GemmPlan plan_ring(int M, int N, int K, bool silu, int max_splits, bool* one_round = nullptr) {
   const int KU = K / 64, units = N / 16, mt = (M + 15) / 16;
+  const double hbm = static_cast<double>(N) * K * (silu ? 4 : 2) / 7.2e6;
   GemmPlan best{kKRing, 1};
   double best_cost = 1e300;
   for (int R : {2, 4, 6, 8, 10}) {
@@ -1165,8 +1168,8 @@ GemmPlan plan_ring(int M, int N, int K, bool silu, int max_splits, bool* one_rou
     for (int S = 1; S <= s_max; ++S) {
       if (even_splits(KU, S) != S) continue;
       const int rounds = (nb * S + 255) / 256, wave_units = ((KU + S - 1) / S + 3) / 4;
-      const double cost = rounds * (8.0 + wave_units * (0.011 * R + 0.028 * mt) + 0.08 * R * mt) +
-                          (silu ? 0.0 : S * static_cast<double>(M) * N / 2.1e7);
+      const double cu = rounds * (wave_units * 0.115 * (R + mt) + 0.068 * R * mt + 1.4);
+      const double cost = std::sqrt(cu * cu + hbm * hbm) + (silu ? 0.0 : S * (static_cast<double>(M) * N * 2.5e-6 + 0.15));
       if (cost < best_cost) {
         best_cost = cost;
         best = GemmPlan{kKRing, S, R};
@@ -1265,7 +1268,7 @@ void launch_tiled(const GemmArgs& a, int bm, int bn, int n_lo, int n_hi, hipStre
 //    the register ring from 14M weights (it runs several blocks per CU: the
 //    0.5B head takes 44 against 52 us; 7B q/k/v 8.7 against 9.4); the
 //    streaming kernels for smaller matrices, where launch latency dominates.
-GemmPlan plan_gemm(int bf16, int M, int N, int K, bool silu, int max_splits) {
+GemmPlan make_plan(int bf16, int M, int N, int K, bool silu, int max_splits) {
   if (!bf16) return {kKF32, 1};
   if (M > 64) return plan_tiled(M, N, K, silu, 1, silu ? 1 : std::max(1, std::min(std::min(16, max_splits), K / kGBK / 2)));
   const double work = static_cast<double>(N) * K * (silu ? 2 : 1);
@@ -1289,6 +1292,19 @@ GemmPlan plan_gemm(int bf16, int M, int N, int K, bool silu, int max_splits) {
   if (silu) return {kKStream, 1};
   if (N >= 16384) return {M <= 8 ? kKStream : kKSkinny32, 1};
   return {kKSkinny16, pick(N / 64, 512)};
+}
+
+// The plan of a shape, remembered per thread: a decode step asks for the same few shapes in every layer,
+// and pricing one takes 1-2 us of the host's time per launch.
+GemmPlan plan_gemm(int bf16, int M, int N, int K, bool silu, int max_splits) {
+  struct Entry { int bf16 = -1, M = 0, N = 0, K = 0, silu = 0, max_splits = 0; GemmPlan plan{}; };
+  thread_local Entry memo[32];
+  const uint32_t h = (static_cast<uint32_t>(M) * 2654435761u) ^ (static_cast<uint32_t>(N) * 40503u) ^
+                     (static_cast<uint32_t>(K) * 2246822519u) ^ static_cast<uint32_t>(max_splits * 7 + silu);
+  Entry& e = memo[(h >> 16 ^ h) & 31];
+  if (e.bf16 != bf16 || e.M != M || e.N != N || e.K != K || e.silu != silu || e.max_splits != max_splits)
+    e = Entry{bf16, M, N, K, silu, max_splits, make_plan(bf16, M, N, K, silu, max_splits)};
+  return e.plan;
 }
 
 }  // namespace
