@@ -898,7 +898,16 @@ int32_t Engine::decode_step(const int32_t* forced, float* logits_out, int64_t* r
   }
   if (bf16_) {
     // One descriptor per item, the longest first (by pages, counted per length), so that the last
-    // blocks to start are the short ones.
+    // blocks to start are the short ones.  When every block has a place at once but some CUs get two (the
+    // first 256 blocks go to one CU each), the second ones are folded back: the longest items alone,
+    // the next longest beside the shortest.
+    const int cus = std::max(1, 256 / cfg_.n_kv_heads), second = total_splits - cus;
+    const bool fold = second > 0 && second <= cus;
+    auto place = [&](int rank) {
+      if (!fold) return rank;
+      const int alone = cus - second;
+      return rank < alone ? second + rank : rank < cus ? rank - alone : cus + (total_splits - 1 - rank);
+    };
     std::vector<int32_t>& at = item_at_;
     const int pmax = tps / kPageTokens;
     at.assign(static_cast<size_t>(pmax) + 2, 0);
@@ -912,7 +921,7 @@ int32_t Engine::decode_step(const int32_t* forced, float* logits_out, int64_t* r
       const int n = (pos[i] + tps - 1) / tps;
       for (int j = 0; j < n; ++j) {
         const int end = std::min(j * tps + tps, pos[i]);
-        int32_t* d4 = desc + 4 * static_cast<size_t>(at[pmax - (end - j * tps + kPageTokens - 1) / kPageTokens]++);
+        int32_t* d4 = desc + 4 * static_cast<size_t>(place(at[pmax - (end - j * tps + kPageTokens - 1) / kPageTokens]++));
         d4[0] = i | (n == 1 ? (1 << 30) : 0) | (j + 1 == n ? (1 << 29) : 0);
         d4[1] = j * tps;
         d4[2] = end;
