@@ -6,25 +6,19 @@
 // accumulation and W as the 16-row "A" operand, activations as the
 // 16-column "B" operand, so one MFMA yields a [16 n, 16 m] tile of C^T.
 //
-//  * k_gemm_deep (M <= 16, large weight matrices): weights stream
-//    from HBM through buffer loads into a ring of register stages; a stage
-//    is a 64-wide K unit in which each lane reads 32 contiguous bytes of a
+//  * k_gemm_ring (up to 64 rows): a block's 4 waves take interleaved 64-wide K units of
+//    the same weight rows; weights and activations are copied into per-wave LDS
+//    rings, and the waves reduce through LDS; blockIdx.y splits K further and
+//    writes fp32 partials that the consumer kernel sums.
+//  * k_gemm_deep (M <= 16, mid-sized weight matrices and large vocabularies): the same split
+//    of the work with weights in a ring of register stages; a stage is a
+//    64-wide K unit in which each lane reads 32 contiguous bytes of a
 //    row, so one wave's two back-to-back loads cover the row's whole
-//    128-byte line.  With the packed copy of the weights (launch_pack_weights)
-//    each load instruction reads one contiguous 1 KB run instead, non-temporal
-//    (the weights are read once per step), the same operands in every lane.  Activations (L2-resident) are loaded one stage ahead
-//    into a single buffer.  The block's 4 waves take interleaved K units and
-//    reduce through LDS; blockIdx.y splits K further (fp32 partials).
-//  * k_gemm_ring (17-64 rows, and the largest products of fewer): the same split of
-//    the work, weights and activations copied into per-wave LDS rings.
-//  * k_gemm_stream, k_gemm_skinny (M <= 16, small matrices): the weights are streamed
-//    once from HBM straight into registers; every lane loads 64 contiguous
-//    bytes per row per 128-wide K chunk (the K order inside a chunk is
-//    permuted identically for both operands, which leaves the dot products
-//    unchanged).  The 4 waves of a k_gemm_stream block split the chunk range and reduce
-//    through LDS, those of a k_gemm_skinny block own different rows and share the
-//    activations; blockIdx.y splits K further and writes fp32 partials that
-//    the consumer kernel sums.
+//    128-byte line.  Activations (L2-resident) are loaded one stage ahead
+//    into a single buffer.
+//    With the packed copy of the weights (launch_pack_weights)
+//    each load instruction of either reads one contiguous 1 KB run instead, non-temporal
+//    (the weights are read once per step), the same operands in every lane.
 //  * k_gemm_tiled (M > 64: prefill and large decode batches): 128- or
 //    256-row x 128- or 256-row block tiles of 32x32x16 MFMAs, half tiles
 //    copied from global memory straight into a swizzled LDS ring.
@@ -70,236 +64,6 @@ __device__ __forceinline__ float silu_fast(float z) {
 }
 // fp32 -> bf16 storage, round to nearest even (v_cvt_pk_bf16_f32).
 __device__ __forceinline__ bf16_t bf16_of(float f) { return __builtin_bit_cast(bf16_t, static_cast<__bf16>(f)); }
-
-// ---- decode-regime weight streaming ----------------------------------------
-template <int R, int MT, bool SILU>
-__global__ __launch_bounds__(256) void k_gemm_stream(GemmArgs a, int chunks_per_split) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int g = lane >> 4, r = lane & 15;
-  const int K = a.K;
-  const int bx = blockIdx.x, m0 = 0;
-  const bf16_t* wrow[R];
-#pragma unroll
-  for (int t = 0; t < R; ++t) {
-    if (SILU) {
-      wrow[t] = static_cast<const bf16_t*>(a.W.ptr[t]) + static_cast<size_t>(bx * 16 + r) * K;
-    } else {
-      wrow[t] = seg_row<bf16_t>(a.W, (bx * R + t) * 16 + r, K);
-    }
-  }
-  const bf16_t* arow[MT];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
-    int m = m0 + mt * 16 + r;
-    if (m >= a.M) m = a.M - 1;
-    arow[mt] = static_cast<const bf16_t*>(a.A) + static_cast<size_t>(m) * a.lda;
-  }
-  f32x4_t acc[R][MT];
-#pragma unroll
-  for (int t = 0; t < R; ++t)
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[t][mt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-  // Register double buffering: the loads of the wave's next chunk are in
-  // flight while the MFMAs of the current one run.
-  bf16x8_t wv[2][R][4], av[2][MT][4];
-  auto load = [&](int buf, int chunk) {
-    const int k = chunk * 128 + g * 32;
-#pragma unroll
-    for (int t = 0; t < R; ++t)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) wv[buf][t][j] = load_bf16x8(wrow[t] + k + 8 * j);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) av[buf][mt][j] = load_bf16x8(arow[mt] + k + 8 * j);
-  };
-  auto compute = [&](int buf) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int t = 0; t < R; ++t)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[t][mt] = mfma16x16x32(wv[buf][t][j], av[buf][mt][j], acc[t][mt]);
-  };
-  const int n_chunks = K / 128;
-  const int c0 = blockIdx.y * chunks_per_split;
-  const int c1 = min(c0 + chunks_per_split, n_chunks);
-  int c = c0 + wave;
-  if (c < c1) load(0, c);
-  for (; c < c1; c += 8) {
-    if (c + 4 < c1) load(1, c + 4);
-    compute(0);
-    if (c + 4 >= c1) break;
-    if (c + 8 < c1) load(0, c + 8);
-    compute(1);
-  }
-
-  constexpr int NSL = R * MT * 4;
-  __shared__ float red[4][NSL][64];
-#pragma unroll
-  for (int t = 0; t < R; ++t)
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) red[wave][(t * MT + mt) * 4 + e][lane] = acc[t][mt][e];
-  __syncthreads();
-
-  if (!SILU) {
-    for (int q = threadIdx.x; q < NSL * 64; q += 256) {
-      const int ln = q & 63, sl = q >> 6;
-      const int e = sl & 3, tm = sl >> 2, mt = tm % MT, t = tm / MT;
-      const int m = m0 + mt * 16 + (ln & 15);
-      if (m < a.M) {
-        const float v = red[0][sl][ln] + red[1][sl][ln] + red[2][sl][ln] + red[3][sl][ln];
-        const int n = (bx * R + t) * 16 + (ln >> 4) * 4 + e;
-        a.part[(static_cast<size_t>(blockIdx.y) * a.M + m) * a.N + n] = v;
-      }
-    }
-  } else {
-    bf16_t* out = static_cast<bf16_t*>(a.act_out);
-    for (int q = threadIdx.x; q < MT * 4 * 64; q += 256) {
-      const int ln = q & 63, sl = q >> 6;
-      const int e = sl & 3, mt = sl >> 2;
-      const int m = m0 + mt * 16 + (ln & 15);
-      if (m < a.M) {
-        const int sg = mt * 4 + e, su = (MT + mt) * 4 + e;
-        const float gv = red[0][sg][ln] + red[1][sg][ln] + red[2][sg][ln] + red[3][sg][ln];
-        const float uv = red[0][su][ln] + red[1][su][ln] + red[2][su][ln] + red[3][su][ln];
-        const int i = bx * 16 + (ln >> 4) * 4 + e;
-        out[static_cast<size_t>(m) * a.N + i] = f32_to_bf16(silu(gv) * uv);
-      }
-    }
-  }
-}
-
-// ---- decode-regime weight streaming with the activations shared in LDS ------
-// The 4 waves of a block own different weight rows and the same K range, so
-// each 128-wide activation chunk is fetched once per block into LDS (double
-// buffered) and read by all waves; weights stream into registers, double
-// buffered.  Wave w owns rows (blockIdx.x*4 + w)*16R .. +16R, or, with the
-// SiLU epilogue, output indices (blockIdx.x*4 + w)*16 .. +16 (gate and up).
-constexpr int kSkLd = 128 + 8;  // padded LDS row of one activation chunk (elements)
-
-template <int R, int MT, bool SILU>
-__global__ __launch_bounds__(256) void k_gemm_skinny(GemmArgs a, int chunks_per_split) {
-  constexpr int AROWS = MT * 16;
-  __shared__ __attribute__((aligned(16))) bf16_t As[2][AROWS * kSkLd];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int g = lane >> 4, r = lane & 15;
-  const int K = a.K;
-  const int unit = blockIdx.x * 4 + wave;
-  const bf16_t* wrow[R];
-#pragma unroll
-  for (int t = 0; t < R; ++t) {
-    if (SILU) wrow[t] = static_cast<const bf16_t*>(a.W.ptr[t]) + static_cast<size_t>(unit * 16 + r) * K;
-    else wrow[t] = seg_row<bf16_t>(a.W, (unit * R + t) * 16 + r, K);
-  }
-  // activation chunk loader: AROWS rows x 16 pieces of 16 bytes, MT pieces per thread
-  const bf16_t* asrc[MT];
-  int aoff[MT];
-#pragma unroll
-  for (int i = 0; i < MT; ++i) {
-    const int q = tid + 256 * i;
-    const int row = q >> 4, col = (q & 15) * 8;
-    int m = row < a.M ? row : a.M - 1;
-    asrc[i] = static_cast<const bf16_t*>(a.A) + static_cast<size_t>(m) * a.lda + col;
-    aoff[i] = row * kSkLd + col;
-  }
-  f32x4_t acc[R][MT];
-#pragma unroll
-  for (int t = 0; t < R; ++t)
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[t][mt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-  bf16x8_t wv[2][R][4];
-  uint4 areg[MT];
-  auto load_w = [&](int buf, int chunk) {
-    const int k = chunk * 128 + g * 32;
-#pragma unroll
-    for (int t = 0; t < R; ++t)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) wv[buf][t][j] = load_bf16x8(wrow[t] + k + 8 * j);
-  };
-  auto load_a = [&](int chunk) {
-#pragma unroll
-    for (int i = 0; i < MT; ++i) areg[i] = *reinterpret_cast<const uint4*>(asrc[i] + chunk * 128);
-  };
-  auto store_a = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < MT; ++i) *reinterpret_cast<uint4*>(&As[buf][aoff[i]]) = areg[i];
-  };
-  auto compute = [&](int wbuf, int abuf) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      bf16x8_t af[MT];
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) af[mt] = load_bf16x8(&As[abuf][(mt * 16 + r) * kSkLd + g * 32 + j * 8]);
-#pragma unroll
-      for (int t = 0; t < R; ++t)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[t][mt] = mfma16x16x32(wv[wbuf][t][j], af[mt], acc[t][mt]);
-    }
-  };
-
-  const int n_chunks = K / 128;
-  const int c0 = blockIdx.y * chunks_per_split;
-  const int c1 = min(c0 + chunks_per_split, n_chunks);
-  // Vector-memory loads complete in issue order, so the next activation
-  // chunk is issued before the next weight chunk: storing it to LDS at the end
-  // of the step then waits only for the activations (an L2 hit), never for
-  // weights still in flight from HBM.
-  if (c0 < c1) {
-    load_a(c0);
-    load_w(0, c0);
-    store_a(0);
-  }
-  __syncthreads();
-  for (int c = c0; c < c1; c += 2) {
-    // even step: W buffer 0, A buffer 0
-    if (c + 1 < c1) {
-      load_a(c + 1);
-      asm volatile("" ::: "memory");
-      load_w(1, c + 1);
-    }
-    compute(0, 0);
-    if (c + 1 < c1) store_a(1);
-    __syncthreads();
-    if (c + 1 >= c1) break;
-    // odd step: W buffer 1, A buffer 1
-    if (c + 2 < c1) {
-      load_a(c + 2);
-      asm volatile("" ::: "memory");
-      load_w(0, c + 2);
-    }
-    compute(1, 1);
-    if (c + 2 < c1) store_a(0);
-    __syncthreads();
-  }
-
-  // lane (g, c) holds C^T[row base + t*16 + 4g + e][m = mt*16 + c]
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
-    const int m = mt * 16 + r;
-    if (m >= a.M) continue;
-    if (SILU) {
-      const int i0 = unit * 16 + g * 4;
-      uint2 pk;
-      pk.x = static_cast<uint32_t>(f32_to_bf16(silu(acc[0][mt][0]) * acc[1][mt][0])) |
-             (static_cast<uint32_t>(f32_to_bf16(silu(acc[0][mt][1]) * acc[1][mt][1])) << 16);
-      pk.y = static_cast<uint32_t>(f32_to_bf16(silu(acc[0][mt][2]) * acc[1][mt][2])) |
-             (static_cast<uint32_t>(f32_to_bf16(silu(acc[0][mt][3]) * acc[1][mt][3])) << 16);
-      *reinterpret_cast<uint2*>(static_cast<bf16_t*>(a.act_out) + static_cast<size_t>(m) * a.N + i0) = pk;
-    } else {
-#pragma unroll
-      for (int t = 0; t < R; ++t) {
-        const int n = (unit * R + t) * 16 + g * 4;
-        *reinterpret_cast<float4*>(a.part + (static_cast<size_t>(blockIdx.y) * a.M + m) * a.N + n) =
-            make_float4(acc[t][mt][0], acc[t][mt][1], acc[t][mt][2], acc[t][mt][3]);
-      }
-    }
-  }
-}
 
 // ---- decode-regime weight streaming, deep register pipeline ----------------
 // Block: 4 waves on the same 16R weight rows (with the SiLU epilogue: R/2
@@ -483,8 +247,8 @@ __global__ __launch_bounds__(256) void k_gemm_deep(GemmArgs a, int units_per_spl
 
 // ---- decode-regime weight streaming through private LDS rings ---------------
 // k_gemm_deep's work split (4 waves on the same R weight fragments, K units
-// interleaved over the waves, no barrier until the end) for 17-64 activation
-// rows.  There a register ring starves: a stage's MFMAs and the wait for the
+// interleaved over the waves, no barrier until the end).  From 17 activation
+// rows on, a register ring starves: a stage's MFMAs and the wait for the
 // next stage's activations run while one stage of weights is in flight (R = 10
 // fragments x 4 activation tiles leave no registers for more), and gate/up of
 // the 7B took 62 us at 64 rows against 46 at 16.  Here weights and activations are copied
@@ -1015,24 +779,9 @@ void launch_f32(const GemmArgs& a, hipStream_t s) {
   else launch_f32_t<4, SILU>(a, s);
 }
 
-template <bool SILU>
-void launch_stream(const GemmArgs& a, hipStream_t s) {
-  const int n_chunks = a.K / 128;
-  const int cps = (n_chunks + a.splits - 1) / a.splits;
-  const int blocks = SILU ? a.N / 16 : a.N / 32;
-  launch_kernel((k_gemm_stream<2, 1, SILU>), dim3(blocks, a.splits), dim3(256), 0, s, a, cps);
-}
-
-template <int R>
-void launch_skinny(const GemmArgs& a, hipStream_t s) {
-  const int n_chunks = a.K / 128;
-  const int cps = (n_chunks + a.splits - 1) / a.splits;
-  launch_kernel((k_gemm_skinny<R, 1, false>), dim3(a.N / (64 * R), a.splits), dim3(256), 0, s, a, cps);
-}
-
 constexpr int kMaxSplitsAny = 64;
 
-enum GemmKernel { kKNone = 0, kKStream = 1, kKSkinny16 = 2, kKSkinny32 = 3, kKTiled = 4, kKF32 = 5, kKDeep = 6, kKRing = 7 };
+enum GemmKernel { kKNone, kKTiled, kKF32, kKDeep, kKRing };
 
 struct GemmPlan {
   int kernel = kKNone;
@@ -1262,36 +1011,25 @@ void launch_tiled(const GemmArgs& a, int bm, int bn, int n_lo, int n_hi, hipStre
 //    takes 47.6 against 61.9 us for the register ring, the 0.5B head 78.7
 //    against 111 us, the 0.5B q/k/v and o 5.2 against 9.8 us for the streaming
 //    kernels; at 17-32 rows the gains are 0-10% at 7B and 40% at 0.5B.
-//  * up to 16 rows: the ring for products of 60M weights and more that one
-//    round of blocks covers (7B gate/up 45.0 against 45.8 us, 32B down 44.1
-//    against 46.2), and for a small model's gate/up from 9 rows (7.1 against 8.2);
-//    the register ring from 14M weights (it runs several blocks per CU: the
-//    0.5B head takes 44 against 52 us; 7B q/k/v 8.7 against 9.4); the
-//    streaming kernels for smaller matrices, where launch latency dominates.
+//  * up to 16 rows: the ring for products under 14M weights: alone and with
+//    warm weights it ties with kernels that stream weights and activations
+//    straight into registers, but within a step, whose weights come from HBM
+//    every time, it keeps more of them in flight (the 0.5B model at 1-16 rows
+//    0.91-0.99 ms a step against 1.02-1.04).  And the ring where one round of
+//    blocks covers a product of 60M weights and more (7B gate/up 45.0 against
+//    45.8 us, 32B down 44.1 against 46.2), or from nine rows of 25M and more (two
+//    layers of the 32B model 405.9 against 409.1 us at 12 rows, 411.1 against
+//    416.1 at 16; at one row 401.3 against 398.4).  Else the register ring, which
+//    also runs several blocks per CU (the 0.5B head takes 44 against 52 us; 7B
+//    q/k/v 8.7 against 9.4).
 GemmPlan make_plan(int bf16, int M, int N, int K, bool silu, int max_splits) {
   if (!bf16) return {kKF32, 1};
   if (M > 64) return plan_tiled(M, N, K, silu, 1, silu ? 1 : std::max(1, std::min(std::min(16, max_splits), K / kGBK / 2)));
   const double work = static_cast<double>(N) * K * (silu ? 2 : 1);
-  const bool units = K % 64 == 0 && N % 16 == 0;
-  if (units && (M > 16 || work >= 6.0e7 || (silu && M > 8))) {
-    bool one_round = false;
-    const GemmPlan ring = plan_ring(M, N, K, silu, max_splits, &one_round);
-    if (M > 16 || one_round || work < 1.4e7) return ring;
-  }
-  if (units && work >= 1.4e7) return plan_deep(N, K, silu, max_splits);
-  const int n_chunks = K / 128;
-  auto pick = [&](int blocks, int target) {
-    int s = 1;
-    for (int c : {1, 2, 3, 4, 6, 8, 12, 16}) {
-      s = c;
-      if (blocks * c >= target) break;
-    }
-    s = std::min(std::min(s, max_splits), std::max(1, n_chunks / 2));
-    return even_splits(n_chunks, s);
-  };
-  if (silu) return {kKStream, 1};
-  if (N >= 16384) return {M <= 8 ? kKStream : kKSkinny32, 1};
-  return {kKSkinny16, pick(N / 64, 512)};
+  bool one_round = false;
+  const GemmPlan ring = plan_ring(M, N, K, silu, max_splits, &one_round);
+  if (M > 16 || work < 1.4e7 || (one_round && work >= (M > 8 ? 2.5e7 : 6.0e7))) return ring;
+  return plan_deep(N, K, silu, max_splits);
 }
 
 // The plan of a shape, remembered per thread: a decode step asks for the same few shapes in every layer,
@@ -1348,35 +1086,14 @@ hipError_t launch_gemm(int bf16, const GemmArgs& a, hipStream_t s) {
     if (tp.n_first < a.N) launch_tiled(a, tp.bm2, tp.bn2, tp.n_first, a.N, s);
     return hipGetLastError();
   }
-  if (kernel == kKRing) {
-    // 32-bit buffer offsets of the rings' copies: activations and one fragment's 16 weight rows
-    if (static_cast<int64_t>(a.M) * a.lda * 2 >= (int64_t{1} << 30) || static_cast<int64_t>(a.K) * 32 >= (int64_t{1} << 30))
-      return hipErrorInvalidValue;
-    const bool ok = silu ? launch_ring<true>(a, plan.R, s) : launch_ring<false>(a, plan.R, s);
-    return ok ? hipGetLastError() : hipErrorInvalidValue;
-  }
-  if (kernel == kKDeep) {
-    const bool ok = silu ? launch_deep<true>(a, plan.R, plan.D, s) : launch_deep<false>(a, plan.R, plan.D, s);
-    return ok ? hipGetLastError() : hipErrorInvalidValue;
-  }
-  if (a.K % 128 != 0) return hipErrorInvalidValue;
-  switch (kernel) {
-    case kKStream:
-      if (a.N % (silu ? 16 : 32) != 0) return hipErrorInvalidValue;
-      if (silu) launch_stream<true>(a, s);
-      else launch_stream<false>(a, s);
-      break;
-    case kKSkinny16:
-      if (a.N % 64 != 0) return hipErrorInvalidValue;
-      launch_skinny<1>(a, s);
-      break;
-    case kKSkinny32:
-      if (a.N % 128 != 0) return hipErrorInvalidValue;
-      launch_skinny<2>(a, s);
-      break;
-    default:
-      return hipErrorInvalidValue;
-  }
+  if (a.K % 64 != 0 || a.N % 16 != 0) return hipErrorInvalidValue;
+  // 32-bit buffer offsets: activations, and one fragment's 16 weight rows
+  if (static_cast<int64_t>(a.M) * a.lda * 2 >= (int64_t{1} << 30) || static_cast<int64_t>(a.K) * 32 >= (int64_t{1} << 30))
+    return hipErrorInvalidValue;
+  bool ok = false;
+  if (kernel == kKRing) ok = silu ? launch_ring<true>(a, plan.R, s) : launch_ring<false>(a, plan.R, s);
+  else if (kernel == kKDeep) ok = silu ? launch_deep<true>(a, plan.R, plan.D, s) : launch_deep<false>(a, plan.R, plan.D, s);
+  if (!ok) return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
