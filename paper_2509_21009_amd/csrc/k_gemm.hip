@@ -49,20 +49,20 @@ __device__ __forceinline__ const T* seg_row(const WSeg& W, int n, int K) {
 }
 
 __device__ __forceinline__ float silu(float z) { return z / (1.0f + expf(-z)); }
-// The same for results that are rounded to bf16, in 14 instructions instead of about 35: exp(-z) as
-// 2^t (1 + d ln 2) with t the rounded product -z log2(e) and d what it is off by (bounded, so that
-// infinities pass), and the quotient z r corrected once by its own remainder: at most 2.2e-7
-// off over [-80, 100], 4.3e-8 in the root mean square (the full sequence 1.8e-7 and 4.0e-8), and of 16.8M
-// values 142 round to another bf16 than the exact ones (143).  0.5B gate/up at 9,216 rows 163
-// against 172 us, 7B 1,937 against 1,970.  Infinities leave a NaN remainder, which the bound turns into
-// a finite one: an infinite quotient or a zero one stays.
+// The same for results that are rounded to bf16, in 15 instructions instead of about 35: exp(-z) as
+// 2^t (1 + dl) with t the rounded product -z log2(e) and dl = d ln 2 from what it is off by (bounded, so
+// that infinities pass), and the quotient z / (1 + 2^t) corrected once by its remainder, which takes dl and what
+// the sum 1 + 2^t lost in: at most 1.8e-7 off over [-80, 100], 3.4e-8 in the root mean
+// square, and of 16.8M values 134 round to another bf16 than the exact ones (the full sequence 1.8e-7, 4.0e-8, 143).
+// 0.5B gate/up at 9,216 rows 163 against 172 us, 7B 1,937 against 1,970.  Infinities leave a NaN
+// remainder, which the bound turns into a finite one: an infinite quotient or a zero one stays.
 __device__ __forceinline__ float silu_fast(float z) {
   constexpr float kL2e = -1.44269504088896341f, kL2eLo = -1.925963033500e-8f, kLn2 = 0.693147180559945309f;
   const float t = z * kL2e;
   const float d = __builtin_amdgcn_fmed3f(__builtin_fmaf(z, kL2eLo, __builtin_fmaf(z, kL2e, -t)), -1e-4f, 1e-4f);
-  const float den = __builtin_fmaf(__builtin_amdgcn_exp2f(t), __builtin_fmaf(d, kLn2, 1.0f), 1.0f);
-  const float r = __builtin_amdgcn_rcpf(den), q = z * r;
-  return __builtin_fmaf(__builtin_amdgcn_fmed3f(__builtin_fmaf(-den, q, z), -3e38f, 3e38f), r, q);
+  const float p = __builtin_amdgcn_exp2f(t), r = __builtin_amdgcn_rcpf(1.0f + p), q = z * r;
+  const float rem = __builtin_fmaf(-(q * p), d * kLn2, __builtin_fmaf(-q, p, z - q));
+  return __builtin_fmaf(__builtin_amdgcn_fmed3f(rem, -3e38f, 3e38f), r, q);
 }
 // fp32 -> bf16 storage, round to nearest even (v_cvt_pk_bf16_f32).
 __device__ __forceinline__ bf16_t bf16_of(float f) { return __builtin_bit_cast(bf16_t, static_cast<__bf16>(f)); }
