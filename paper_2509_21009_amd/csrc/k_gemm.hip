@@ -1034,16 +1034,19 @@ GemmPlan make_plan(int bf16, int M, int N, int K, bool silu, int max_splits) {
   return plan_deep(N, K, silu, max_splits);
 }
 
-// The plan of a shape, remembered per thread: a decode step asks for the same few shapes in every layer,
-// and pricing one takes 1-2 us of the host's time per launch.
+// The plan of a shape, remembered per thread (16 sets of four, the oldest replaced): a decode step asks for
+// the same few shapes in every layer, and pricing one takes 1-2 us of the host's time per launch.
 GemmPlan plan_gemm(int bf16, int M, int N, int K, bool silu, int max_splits) {
   struct Entry { int bf16 = -1, M = 0, N = 0, K = 0, silu = 0, max_splits = 0; GemmPlan plan{}; };
-  thread_local Entry memo[32];
-  const uint32_t h = (static_cast<uint32_t>(M) * 2654435761u) ^ (static_cast<uint32_t>(N) * 40503u) ^
-                     (static_cast<uint32_t>(K) * 2246822519u) ^ static_cast<uint32_t>(max_splits * 7 + silu);
-  Entry& e = memo[(h >> 16 ^ h) & 31];
-  if (e.bf16 != bf16 || e.M != M || e.N != N || e.K != K || e.silu != silu || e.max_splits != max_splits)
-    e = Entry{bf16, M, N, K, silu, max_splits, make_plan(bf16, M, N, K, silu, max_splits)};
+  struct Set { Entry e[4]; unsigned next = 0; };
+  thread_local Set memo[16];
+  uint64_t h = (static_cast<uint64_t>(static_cast<uint32_t>(M)) << 32 | static_cast<uint32_t>(N)) * 0x9e3779b97f4a7c15ull;
+  h = (h ^ static_cast<uint64_t>(static_cast<uint32_t>(K)) << 8 ^ static_cast<uint64_t>(max_splits * 2 + silu)) * 0xd1342543de82ef95ull;
+  Set& set = memo[h >> 60];
+  for (const Entry& e : set.e)
+    if (e.bf16 == bf16 && e.M == M && e.N == N && e.K == K && e.silu == silu && e.max_splits == max_splits) return e.plan;
+  Entry& e = set.e[set.next++ & 3];
+  e = Entry{bf16, M, N, K, silu, max_splits, make_plan(bf16, M, N, K, silu, max_splits)};
   return e.plan;
 }
 
