@@ -16,13 +16,15 @@ __device__ __forceinline__ u32x4_raw raw_rsrc(const void* p, uint32_t bytes) {
   return u32x4_raw{static_cast<uint32_t>(addr), static_cast<uint32_t>(addr >> 32) & 0xffffu, bytes, 0x00020000u};
 }
 // 16 bytes per lane from byte voff of the buffer into LDS at lds + 16 * lane.  M0 holds the LDS base;
-// it is named as clobbered, so the compiler keeps none of its own values there across the load.
+// it is named as clobbered, so the compiler keeps none of its own values there across the load.  gfx9 needs
+// one wait state between a scalar write of M0 and a load to LDS that reads it (the compiler puts it between
+// the two for its builtin, but does not look inside inline assembly).
 __device__ __forceinline__ void dma16(u32x4_raw r, uint32_t lds, int voff) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" : : "s"(lds), "v"(voff), "s"(r) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" : : "s"(lds), "v"(voff), "s"(r) : "memory", "m0");
 }
 // The same, marked non-temporal: for data that is read once and should not displace reused lines.
 __device__ __forceinline__ void dma16_nt(u32x4_raw r, uint32_t lds, int voff) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds" : : "s"(lds), "v"(voff), "s"(r) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds" : : "s"(lds), "v"(voff), "s"(r) : "memory", "m0");
 }
 // s_waitcnt vmcnt(N), the other counters at their maxima (gfx9 encoding).
 template <int N>
