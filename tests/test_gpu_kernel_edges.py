@@ -9,6 +9,7 @@ import dataclasses
 import numpy as np
 import pytest
 
+from oracle import model as om
 from tests.gpu_helpers import rp, teacher_forced_parity
 from workloads import ModelShape, make_weights, weights_to_numpy
 from workloads.gen import Workload
@@ -102,3 +103,38 @@ def test_decode_gemm_wide(rows, pack):
     rows) and a ragged head of 8,320 rows; at 397 rows gate/up in two launches of different tiles."""
     shape = ModelShape("wide", 1, 3584, 28, 4, 128, 18944, 8320, False, "bf16")
     _parity(shape, [1 + i % 3 for i in range(rows)], 2, max_prefill=1024, pack=pack, check=[0, rows // 2, rows - 1])
+
+
+@pytest.mark.parametrize("plens", [[40, 41, 42], [1] * 20])
+def test_silu_of_large_negative_gates(plens):
+    """SiLU down to where exp(-z) overflows: at gates of -87.3 to -88.7 its values, -1e-36 to -2e-37, are normal
+    bf16 numbers.  Gates of -88.5 to -86 on up values of 1e36 give activations of order one, so a
+    product that flushed them to zero would miss the oracle's logits by 0.22 (below -88.72 exp(-z) is infinite
+    in fp32, and the result zero).  The attention output is zero and every token's hidden state has the same two large entries, which alone meet the gate and up
+    weights: the bf16 rounding of the hidden state (the oracle rounds there too) fixes the gates."""
+    s = dataclasses.replace(SMALL, vocab=640)
+    wd = make_weights(s, seed=5, device=DEV)
+    gen = torch.Generator(device=DEV).manual_seed(1)
+    e = (torch.randint(0, 2, (s.vocab, s.hidden), generator=gen, device=DEV) * 2 - 1) / 64.0
+    e[:, 0], e[:, 1] = 1.0, 0.125
+    wd["embed"].copy_(e)
+    L = wd["layers"][0]
+    L["wo"].zero_()
+    for k in ("w_gate", "w_up"):
+        L[k].zero_()
+    h0 = float((1.0 / torch.sqrt((e[0].double() ** 2).mean() + 1e-6)))
+    assert abs(h0 / 0.125 % 1.0 - 0.5) > 0.01  # not beside a rounding boundary of bf16 (steps of 1/8 from 16 to 32)
+    h0 = round(h0 * 8) / 8
+    L["w_gate"][:, 0] = -88.0 / h0
+    L["w_gate"][:, 1] = torch.linspace(-0.5, 2.0, s.inter, device=DEV) / (h0 / 8)
+    L["w_up"][:, 0] = 1e36 / h0
+    gates = L["w_gate"][:, :2].double() @ torch.tensor([h0, h0 / 8], dtype=torch.float64, device=DEV)
+    assert float(gates.min()) > -88.6 and int((gates < -87.4).sum()) > 100
+    w64 = weights_to_numpy(wd)
+    wl = _workload(s, plens, sum(plens))
+    R = rp()
+    eng = R.Engine(s, R.weights_for_engine(wd), max_seqs=len(plens), max_prefill_tokens=256, max_context=64,
+                   kv_pages=len(plens))
+    r = teacher_forced_parity(eng, s, w64, wl, 3, 2e-2, 1.0, 11, rnd=om.bf16_round)
+    eng.close()
+    assert r.max_rel_err <= 2e-2 and r.id_mismatch == 0, r
