@@ -645,25 +645,31 @@ __global__ __launch_bounds__((64 * TiledCfg<BM, BN>::WAVES)) void k_gemm_tiled(G
   wait_vmcnt<0>();  // no copy may land in this block's LDS after it ends
 
   // acc register e of tile (ah, mt): m = ah BM/2 + (wm MT + mt) 32 + 8 (e/4) + 4 lh + e%4, n = bh BN/2 + wn 32 + l32.
-  // Stores go through a resource over the tile's rows, which drops rows past M; columns past N start
-  // out of range.  (A branch per element doubled the kernel's code: 2-3 us of instruction fetch a launch.)
+  // Stores go through a resource over the 32 rows of an (ah, mt) tile, which drops rows past M; columns past N
+  // start out of range.  (A branch per element doubled the kernel's code: 2-3 us of instruction fetch a launch.)
+  // Offsets are 32-bit, so the rows of a resource are few: 32 rows of up to 2^24 columns stay below kOut.
   constexpr int ESZ = SILU ? 2 : 4, kOut = static_cast<int>(0x80000000u);
-  const int rows = min(BM, a.M - mb * BM);
   char* out = SILU ? static_cast<char*>(a.act_out) : reinterpret_cast<char*>(a.part + static_cast<size_t>(split) * a.M * a.N);
-  const __amdgpu_buffer_rsrc_t ors = buffer_rsrc(out + static_cast<size_t>(mb) * BM * a.N * ESZ, static_cast<uint32_t>(rows) * a.N * ESZ);
   int voff[2];
 #pragma unroll
   for (int bh = 0; bh < (SILU ? 1 : 2); ++bh) {
     const int n = SILU ? nb * (BN / 2) + wn * 32 + l32 : nb * BN + bh * (BN / 2) + wn * 32 + l32;
-    voff[bh] = n < a.N ? ((wm * MT * 32 + 4 * lh) * a.N + n) * ESZ : kOut;
+    voff[bh] = n < a.N ? (4 * lh * a.N + n) * ESZ : kOut;
   }
 #pragma unroll
   for (int ah = 0; ah < 2; ++ah)
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int mt = 0; mt < MT; ++mt) {
+      const int m0 = mb * BM + ah * (BM / 2) + (wm * MT + mt) * 32, rows = max(min(32, a.M - m0), 0);
+      const uint64_t base = reinterpret_cast<uint64_t>(out) + static_cast<uint64_t>(m0) * static_cast<uint32_t>(a.N * ESZ);
+      const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(base)),  // scalar: else a loop per store
+                     hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(base >> 32));
+      const __amdgpu_buffer_rsrc_t ors =
+          buffer_rsrc(reinterpret_cast<void*>(static_cast<uint64_t>(hi) << 32 | lo),
+                      __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(rows) * static_cast<uint32_t>(a.N * ESZ)));
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
-        const int row = (ah * (BM / 2) + mt * 32 + 8 * (e >> 2) + (e & 3)) * a.N * ESZ;
+        const int row = (8 * (e >> 2) + (e & 3)) * a.N * ESZ;
         if (SILU) {
           __builtin_amdgcn_raw_buffer_store_b16(bf16_of(silu_fast(acc[ah][0][mt][e]) * acc[ah][1][mt][e]), ors, voff[0] + row, 0, 0);
         } else {
@@ -672,6 +678,7 @@ __global__ __launch_bounds__((64 * TiledCfg<BM, BN>::WAVES)) void k_gemm_tiled(G
             __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[ah][bh][mt][e]), ors, voff[bh] + row, 0, 0);
         }
       }
+    }
 }
 
 // ---- fp32 model ------------------------------------------------------------
@@ -1084,7 +1091,7 @@ hipError_t launch_gemm(int bf16, const GemmArgs& a, hipStream_t s) {
   if (kernel == kKTiled) {
     if (a.K % kGBK != 0 || (silu && a.N % 128 != 0) || (!silu && a.N % 8 != 0)) return hipErrorInvalidValue;
     // 32-bit buffer offsets; every weight segment but the last a whole number of 16-row blocks
-    if (static_cast<int64_t>(a.M + 256) * a.lda * 2 >= (int64_t{1} << 31)) return hipErrorInvalidValue;
+    if (static_cast<int64_t>(a.M + 256) * a.lda * 2 >= (int64_t{1} << 31) || a.N >= 1 << 24) return hipErrorInvalidValue;
     for (int sg = 0; sg < a.W.n_seg; ++sg) {
       if (static_cast<int64_t>(a.W.rows[sg]) * a.K * 2 >= (int64_t{1} << 31)) return hipErrorInvalidValue;
       if (!silu && sg < a.W.n_seg - 1 && a.W.rows[sg] % 16 != 0) return hipErrorInvalidValue;

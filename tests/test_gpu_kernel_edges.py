@@ -138,3 +138,30 @@ def test_silu_of_large_negative_gates(plens):
     r = teacher_forced_parity(eng, s, w64, wl, 3, 2e-2, 1.0, 11, rnd=om.bf16_round)
     eng.close()
     assert r.max_rel_err <= 2e-2 and r.id_mismatch == 0, r
+
+
+def test_tiled_gemm_of_more_than_two_million_columns():
+    """A head of 4,194,688 rows: 256 rows of fp32 logits span more than 4 GiB, past what a 32-bit offset over
+    a whole 256-row tile reaches.  The tiled GEMM's logits (256 prompts at once) against the ring GEMM's, which
+    addresses row by row (64 at a time).  The two sum the layer's products in other orders; both are held to 2e-2
+    of the oracle elsewhere, so to 4e-2 of each other here."""
+    s = ModelShape("wide-head", 1, 128, 2, 2, 64, 128, (1 << 22) + 384, True, "bf16")
+    wd = make_weights(s, seed=7, device=DEV)
+    R = rp()
+    n = 256
+    toks = np.random.default_rng(3).integers(0, s.vocab, size=n).astype(np.int32)
+    eng = R.Engine(s, R.weights_for_engine(wd), max_seqs=n, max_prefill_tokens=n, max_context=4, kv_pages=n)
+
+    def logits(lo, hi):
+        ids = np.arange(lo, hi, dtype=np.int64)
+        out, _ = eng.prefill(ids, toks[lo:hi], np.arange(hi - lo + 1, dtype=np.int64), np.full(hi - lo, 2, np.int32),
+                             1, 1.0, logits=True)
+        eng.abort(ids)
+        return out
+
+    whole = logits(0, n)
+    for lo in range(0, n, 64):
+        part = logits(lo, lo + 64)
+        err = (whole[lo:lo + 64] - part).abs().amax(1) / part.abs().amax(1)
+        assert float(err.max()) <= 4e-2, (lo, err)
+    eng.close()
