@@ -25,7 +25,8 @@ import statistics
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SOURCE = "paper_2509_21009_amd/csrc/k_gemm.hip"
-COMMON = "paper_2509_21009_amd/csrc/device_common.hpp"
+PLANS = "paper_2509_21009_amd/csrc/gemm_plan.hpp"
+HELPERS = ("paper_2509_21009_amd/csrc/device_common.hpp", "paper_2509_21009_amd/csrc/lds_dma.hpp")
 
 
 def _between(text: str, start: str, end: str) -> str:
@@ -38,15 +39,16 @@ def deep_source_digest(root: str = ROOT) -> str:
     plans (plan_deep with the instantiated configurations, plan_ring) and the device helpers they use.
     Edits elsewhere in the GEMM source leave it unchanged."""
     gemm = open(os.path.join(root, SOURCE)).read()
+    plans = open(os.path.join(root, PLANS)).read()
     parts = [_between(gemm, "template <bool PACKED>\n__device__ __forceinline__ bf16x8_t load_w16", "\n}\n"),
              _between(gemm, "template <int R, int MT, int D, bool SILU, bool PACKED>\n__global__ __launch_bounds__(256) "
                             "void k_gemm_deep", "\n}\n"),
              _between(gemm, "template <int R, int MT, bool SILU, bool PACKED>\n__global__ __launch_bounds__(256) "
                             "void k_gemm_ring", "\n}\n"),
-             _between(gemm, "GemmPlan plan_ring(", "\n}\n"),
-             _between(gemm, "constexpr DeepCfg kDeepCfg", "\n};\n"),
-             _between(gemm, "GemmPlan plan_deep(", "\n}\n"),
-             open(os.path.join(root, COMMON)).read()]
+             _between(plans, "GemmPlan plan_ring(", "\n}\n"),
+             _between(plans, "constexpr DeepCfg kDeepCfg", "\n};\n"),
+             _between(plans, "GemmPlan plan_deep(", "\n}\n"),
+             *(open(os.path.join(root, h)).read() for h in HELPERS)]
     return hashlib.sha256("\n".join(parts).encode()).hexdigest()
 COPY_BYTES = 1 << 30
 SHAPE = {"H": 3584, "I": 18944}  # Qwen2.5-7B hidden and intermediate sizes

@@ -1,4 +1,4 @@
-// Host-only checks of the KV page pool and the tail-batching planner, built
+// Host-only checks of the KV page pool, the tail-batching planner and the GEMM plans, built
 // with g++ and AddressSanitizer/UndefinedBehaviorSanitizer by the CPU tests.
 #include <cassert>
 #include <algorithm>
@@ -9,6 +9,7 @@
 #include <stdexcept>
 #include <vector>
 
+#include "gemm_plan.hpp"
 #include "kv_pool.hpp"
 #include "tail_batch.hpp"
 
@@ -100,7 +101,43 @@ static void test_plan_invariants() {
   }
 }
 
+// A launch whose split is not the planner's own is planned for the split it has.
+static void test_gemm_plan_for_the_launched_split() {
+  using namespace rollpack;
+  // an unsplit head: two fragments per block give 152 blocks where the plan for three splits would leave 76
+  CHECK(plan_launch(1, 45, 4864, 5120, false, 1).R == 2);
+  CHECK(plan_launch(1, 64, 8320, 3584, false, 1).R == 4);
+  CHECK(plan_launch(1, 8, 4864, 5120, false, 1).kernel == kKRing && plan_launch(1, 8, 8320, 3584, false, 1).kernel == kKDeep);
+  std::mt19937 rng(5);
+  for (int it = 0; it < 4000; ++it) {
+    const int M = 1 + rng() % 600, N = 128 * (1 + rng() % 400), K = 128 * (1 + rng() % 160);
+    const bool silu = rng() % 4 == 0;
+    const GemmPlan own = plan_gemm(1, M, N, K, silu, 1, kMaxSplitsAny);
+    CHECK(own.splits == 1 || !silu);
+    CHECK(own.splits == even_splits(K / kGBK, own.splits) && own.splits <= 16);
+    const int cap = 1 + rng() % 16, s = silu ? 1 : plan_gemm(1, M, N, K, false, 1, cap).splits;
+    CHECK(s <= cap || s == 1);
+    const GemmPlan p = plan_launch(1, M, N, K, silu, s);
+    CHECK(p.splits == s);
+    if (s == own.splits) {
+      CHECK(p.kernel == own.kernel && p.R == own.R && p.D == own.D && p.bm == own.bm && p.bn == own.bn &&
+            p.n_first == own.n_first);
+      continue;
+    }
+    // else the planner's choice at that split
+    if (p.kernel == kKRing) {
+      const GemmPlan ring = plan_ring(M, N, K, silu, s, s);
+      CHECK(ring.R == p.R && ring.splits == s);
+    } else if (p.kernel == kKDeep) {
+      CHECK(M <= 16 && plan_deep(N, K, silu, s, s).R == p.R);
+    } else {
+      CHECK(p.kernel == kKTiled && M > 64 && (p.n_first == N || s == 1));
+    }
+  }
+}
+
 int main() {
+  test_gemm_plan_for_the_launched_split();
   test_pool_random();
   test_pool_misuse();
   test_plan_invariants();

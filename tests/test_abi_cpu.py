@@ -225,7 +225,7 @@ def test_bench_reports_counter_traffic_only_for_the_measured_kernel(tmp_path):
     or kernel differs or the deep kernel's source no longer matches the recorded hash."""
     import json
     import bench
-    from paper_2509_21009_amd.counter_traffic import COMMON, SOURCE, deep_source_digest
+    from paper_2509_21009_amd.counter_traffic import HELPERS, PLANS, SOURCE, deep_source_digest
     rec = {"kernel": "gemm_gate_up", "workload": "7b-long", "source": SOURCE,
            "source_sha256_deep": deep_source_digest(ROOT), "traffic_bytes_per_launch": 123456}
     path = tmp_path / "rec.json"
@@ -236,18 +236,27 @@ def test_bench_reports_counter_traffic_only_for_the_measured_kernel(tmp_path):
     path.write_text(json.dumps(dict(rec, source_sha256_deep="0" * 64)))
     assert bench.measured_traffic("gemm_gate_up", "7b-long", str(path)) is None
     assert bench.measured_traffic("gemm_gate_up", "7b-long", str(tmp_path / "missing.json")) is None
-    # the digest covers the deep kernel and its plan, not the rest of the GEMM source
+    # the digest covers the decode kernels, their plans and their device helpers, not the rest of the GEMM source
     root = tmp_path / "tree"
-    for rel in (SOURCE, COMMON):
+    for rel in (SOURCE, PLANS, *HELPERS):
         (root / rel).parent.mkdir(parents=True, exist_ok=True)
         (root / rel).write_text(open(os.path.join(ROOT, rel)).read())
     base = deep_source_digest(str(root))
     assert base == deep_source_digest(ROOT)
     gemm = (root / SOURCE).read_text()
-    (root / SOURCE).write_text(gemm.replace("constexpr int kGBN = 256", "constexpr int kGBN = 256  /* edit */"))
+    tiled = "__device__ __forceinline__ int gswz(int r) {"
+    assert tiled in gemm
+    (root / SOURCE).write_text(gemm.replace(tiled, tiled + "  /* edit */"))
     assert deep_source_digest(str(root)) == base
     (root / SOURCE).write_text(gemm.replace("const int K = a.K, KU = K / 64;", "const int K = a.K, KU = K / 64;  // edit"))
     assert deep_source_digest(str(root)) != base
+    (root / SOURCE).write_text(gemm)
+    for rel, edit in ((PLANS, "inline GemmPlan plan_ring("), (PLANS, "inline GemmPlan plan_deep("), (HELPERS[1], "s_nop 0")):
+        text = (root / rel).read_text()
+        assert edit in text
+        (root / rel).write_text(text.replace(edit, edit + " "))
+        assert deep_source_digest(str(root)) != base, edit
+        (root / rel).write_text(text)
     # the committed record names the kernel bench.py reports by default
     committed = json.load(open(bench.TRAFFIC_RECORD))
     assert committed["kernel"] == "gemm_gate_up" and committed["workload"] == "7b-long"
