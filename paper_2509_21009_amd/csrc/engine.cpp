@@ -7,6 +7,7 @@
 // All device work is enqueued on one stream; per-step metadata is O(rows)
 // integers copied from pinned staging buffers.
 #include "engine.hpp"
+#include "decode_plan.hpp"
 #include "tail_batch.hpp"
 
 #include <algorithm>
@@ -31,8 +32,6 @@ void hip_check(hipError_t e, const char* what) {
 #define HIP_TRY(expr) hip_check((expr), #expr)
 
 size_t align256(size_t v) { return (v + 255) & ~static_cast<size_t>(255); }
-
-int decode_split_target(const rp_model_config& c) { return std::max(1, 2048 / c.n_kv_heads); }
 
 }  // namespace
 
@@ -85,7 +84,7 @@ ScratchPlan plan_scratch(const rp_model_config& c, const rp_engine_limits& l) {
   const size_t mmax = std::max<size_t>(l.max_prefill_tokens, l.max_seqs);
   const size_t nmax = std::max(nqkv, H);
   p.max_pages = static_cast<int32_t>((l.max_context + kPageTokens - 1) / kPageTokens);
-  p.split_cap = c.dtype == RP_DTYPE_BF16 ? decode_split_target(c) + l.max_seqs : 0;
+  p.split_cap = c.dtype == RP_DTYPE_BF16 ? decode_split_target(c.n_kv_heads) + l.max_seqs : 0;
   p.part_elems = std::max(static_cast<size_t>(l.max_prefill_tokens) * nmax,
                           static_cast<size_t>(kMaxGemmSplits) * l.max_seqs * nmax);
   const size_t T = l.max_prefill_tokens, S = l.max_seqs;
@@ -803,36 +802,6 @@ void Engine::prefill(int32_t n, const int64_t* ids, const int32_t* toks, const i
   }
 }
 
-// Pages of cached keys per decode attention item.  An item is a block of four waves; two blocks fit a CU,
-// which moves a page of one head (K and V, 32 KB at head_dim 128) in about 1.3 us whether it runs one
-// block or two.  The cost of a size, in us: the fullest CU's pages and the items' own ends (2.5 us each),
-// plus, when some row has more than one item, the merge (4.5 us).  Over sizes forced from 1 page to
-// whole rows at 1-330 rows of 64-12,000 tokens (7B, 0.5B and 32B layers) its choices are within 1-2% of
-// the fastest step; the optimum is flat.
-int Engine::decode_pages_per_item(int64_t total_pages, int64_t max_pages, int B) const {
-  const double page_us = cfg_.head_dim == 128 ? 1.3 : 0.65, ends_us = 2.5, merge_us = 4.5;
-  const int64_t target = decode_split_target(cfg_);  // the item capacity: total_pages / pps + B items at most
-  const int64_t least = std::max<int64_t>(1, (total_pages + target - 1) / target);
-  int64_t best = std::max(least, max_pages);
-  double best_us = 1e300;
-  for (int64_t pps = least;; pps += std::max<int64_t>(1, pps / 8)) {
-    pps = std::min(pps, std::max(least, max_pages));
-    const bool merge = pps < max_pages;
-    const double items = merge ? (static_cast<double>(total_pages) / pps + 0.5 * B) * cfg_.n_kv_heads
-                               : static_cast<double>(B) * cfg_.n_kv_heads;
-    const double one = pps * page_us + ends_us;
-    const double all = (static_cast<double>(total_pages) * cfg_.n_kv_heads * page_us + items * ends_us) / 256;
-    // up to one block per CU the longest item ends the step; past that the CUs even out to half an item
-    const double us = (items <= 256 ? one : std::max(one, all + 0.5 * one)) + (merge ? merge_us : 0.0);
-    if (us < best_us) {
-      best_us = us;
-      best = pps;
-    }
-    if (pps >= max_pages) break;
-  }
-  return static_cast<int>(best);
-}
-
 int32_t Engine::decode_step(const int32_t* forced, float* logits_out, int64_t* row_ids_out) {
   if (forced && kv_policy_ == RP_KV_ON_DEMAND)
     throw RpError(RP_ERR_INVALID_ARG, "teacher forcing needs the reserving KV policy");
@@ -864,7 +833,7 @@ int32_t Engine::decode_step(const int32_t* forced, float* logits_out, int64_t* r
   }
   int tps = 0, total_splits = 0;
   if (bf16_) {
-    tps = decode_pages_per_item(total_pages, max_pages, B) * kPageTokens;
+    tps = decode_pages_per_item(cfg_.n_kv_heads, cfg_.head_dim, total_pages, max_pages, B) * kPageTokens;
     max_row_splits_ = 0;
     for (int i = 0; i < B; ++i) {
       const int n = (ctx_h[i] - 1 + tps - 1) / tps;  // over the cached keys; the newest token rides on the last

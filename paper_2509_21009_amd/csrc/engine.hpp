@@ -176,7 +176,6 @@ class Engine {
   void mark(size_t k);
   double mark_ms(size_t a, size_t b);
 
-  int decode_pages_per_item(int64_t total_pages, int64_t max_pages, int B) const;
   void forward(int M, bool is_prefill, int n_seq_prefill, int total_items, int total_splits, int tps);
   int32_t* stage_meta(size_t ints);
   void upload_meta(const int32_t* host, size_t ints);

@@ -1,4 +1,5 @@
-// Host-only checks of the KV page pool, the tail-batching planner and the GEMM plans, built
+// Host-only checks of the KV page pool, the tail-batching planner, the GEMM plans and the decode attention
+// items, built
 // with g++ and AddressSanitizer/UndefinedBehaviorSanitizer by the CPU tests.
 #include <cassert>
 #include <algorithm>
@@ -9,6 +10,7 @@
 #include <stdexcept>
 #include <vector>
 
+#include "decode_plan.hpp"
 #include "gemm_plan.hpp"
 #include "kv_pool.hpp"
 #include "tail_batch.hpp"
@@ -136,7 +138,29 @@ static void test_gemm_plan_for_the_launched_split() {
   }
 }
 
+// Attention items stay within the workspace's capacity for any contexts.
+static void test_decode_items_fit() {
+  std::mt19937 rng(13);
+  for (int it = 0; it < 20000; ++it) {
+    const int n_kv = 1 << rng() % 5, hd = rng() % 2 ? 64 : 128, B = 1 + rng() % (it % 8 ? 16 : 400);
+    const int64_t most = 1 + rng() % (it % 2 ? 1024 : 64);
+    std::vector<int64_t> pages(B);
+    int64_t total = 0, longest = 0;
+    for (auto& p : pages) {
+      p = 1 + rng() % most;
+      total += p;
+      longest = std::max(longest, p);
+    }
+    const int64_t pps = rollpack::decode_pages_per_item(n_kv, hd, total, longest, B);
+    CHECK(pps >= 1);
+    int64_t items = 0;
+    for (int64_t p : pages) items += (p + pps - 1) / pps;
+    CHECK(items <= rollpack::decode_split_target(n_kv) + B);
+  }
+}
+
 int main() {
+  test_decode_items_fit();
   test_gemm_plan_for_the_launched_split();
   test_pool_random();
   test_pool_misuse();

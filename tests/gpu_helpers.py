@@ -1,9 +1,13 @@
 """Shared helpers of the GPU parity tests (imported by tests marked gpu)."""
 from __future__ import annotations
 
+import ctypes
 import dataclasses
+import functools
 import os
+import subprocess
 import sys
+import tempfile
 
 import numpy as np
 
@@ -40,6 +44,24 @@ class ParityResult:
     id_checked: int
     id_mismatch: int
     worst: tuple
+
+
+@functools.lru_cache(maxsize=None)
+def _item_plan():
+    csrc = os.path.join(ROOT, "paper_2509_21009_amd", "csrc")
+    with tempfile.TemporaryDirectory() as d:
+        so = os.path.join(d, "decode_items.so")
+        subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", f"-I{csrc}",
+                        os.path.join(ROOT, "tests", "cpp", "decode_items.cpp"), "-o", so], check=True)
+        return ctypes.CDLL(so).pages_per_item
+
+
+def decode_items(shape, ctx):
+    """(pages per item, items of each row) of a decode step at these contexts, which count the step's
+    own token: the rule the engine compiles (csrc/decode_plan.hpp), built for the host."""
+    ctx = np.ascontiguousarray(ctx, np.int32)
+    pages = _item_plan()(shape.n_kv, shape.head_dim, ctx.ctypes.data_as(ctypes.c_void_p), len(ctx))
+    return pages, -(-(ctx - 1) // (64 * pages))
 
 
 ORACLE_CHUNK = 2048

@@ -13,7 +13,7 @@ import dataclasses
 import numpy as np
 import pytest
 
-from tests.gpu_helpers import log, rp, teacher_forced_parity, to_device
+from tests.gpu_helpers import decode_items, log, rp, teacher_forced_parity, to_device
 from workloads import SHAPES, make_weights, make_workload, truncated, weights_to_numpy
 from oracle import model as om
 
@@ -126,8 +126,9 @@ def test_bf16_against_rounding_oracle():
 def test_bf16_decode_batch_shapes(model, layers, vocab, batches):
     """Decode GEMM regimes by live rows: 1-16, 17-32, 33-48, 49-64 (weight streaming: one
     to four 16-row activation tiles) and 80 (LDS-tiled MFMA).  The 0.5B layer (K = 896 and
-    4864) runs the small-matrix kernels; the 7B layer (K = 3584 and 18944, LM head 8192 x 3584)
-    runs the deep-pipelined ones with their K splits and ragged last blocks."""
+    4864) and the 7B layer (K = 3584 and 18944, LM head 8192 x 3584) run the LDS-ring kernel with
+    its K splits and ragged last blocks; at two rows the 7B's q/k/v product and its unsplit head
+    run the register ring."""
     base = truncated(SHAPES[model], layers, vocab=vocab)
     wd = make_weights(base, seed=1, device=DEV)
     w64 = weights_to_numpy(wd)
@@ -177,9 +178,9 @@ def test_bf16_large_decode_batches(model, batches):
 
 
 def test_long_context_many_splits():
-    """One 4150-token row beside two short ones: its decode context spans 65 pages, so the
-    split-context attention runs 65 work items for that row and the merge walks two chunks
-    of 64 splits; the short rows are single-split items written without a merge."""
+    """One 4150-token row beside two short ones: its decode context spans 65 pages, and the
+    split-context attention runs an item per page, which the 1024-thread merge combines; the short
+    rows are single items written without a merge."""
     s = truncated(SHAPES["qwen2.5-0.5b"], 1, vocab=2048)
     s = dataclasses.replace(s, tied=False)
     wd = make_weights(s, seed=6, device=DEV)
@@ -192,6 +193,8 @@ def test_long_context_many_splits():
     from workloads.gen import Workload
     wl = Workload("long", s, np.array([7, 8, 9], np.int64), np.concatenate(prompts), offs,
                   np.full(3, 4, np.int32), np.arange(3, dtype=np.int32), 1.0, 5)
+    for j in range(1, 4):
+        assert decode_items(s, np.array(plen) + j)[1].tolist() == [65, 1, 1]
     eng = _engine(s, wd, 4, 4200, 4224, 3 * 67)
     r = teacher_forced_parity(eng, s, w64, wl, 4, 2e-2, 1.0, 5)
     eng.close()
@@ -199,12 +202,12 @@ def test_long_context_many_splits():
     assert r.max_rel_err <= 2e-2 and r.id_mismatch == 0, r
 
 
-@pytest.mark.parametrize("plen,kernel", [
-    ([450, 300, 200, 100, 64, 30, 10, 3], "one-wave merge, up to 8 splits"),
-    ([3800, 1900, 700, 300, 130, 65, 20, 5], "one-wave merge, up to 64 splits"),
-    ([4150, 1900, 700, 300, 130, 65, 20, 5], "1024-thread merge (a row of 65 splits)"),
+@pytest.mark.parametrize("plen,kernel,most", [
+    ([450, 300, 200, 100, 64, 30, 10, 3], "one-wave merge, up to 8 splits", 8),
+    ([3800, 1900, 700, 300, 130, 65, 20, 5], "one-wave merge, up to 64 splits", 60),
+    ([4150, 1900, 700, 300, 130, 65, 20, 5], "1024-thread merge (a row of 65 splits)", 65),
 ])
-def test_split_merge_kernels_at_eight_rows(plen, kernel):
+def test_split_merge_kernels_at_eight_rows(plen, kernel, most):
     """Eight decode rows of one-page to 65-page contexts, one split per page: single-split rows
     are written by the decode kernel, the others are merged, from eight rows up by the one-wave
     kernel while no row has more than 64 splits, else by the 1024-thread kernel.  Three rows
@@ -221,6 +224,9 @@ def test_split_merge_kernels_at_eight_rows(plen, kernel):
     n = len(plen)
     wl = Workload("merge", s, np.arange(40, 40 + n, dtype=np.int64), np.concatenate(prompts), offs,
                   np.full(n, 3, np.int32), np.arange(n, dtype=np.int32), 1.0, 6)
+    for j in (1, 2):
+        pages, items = decode_items(s, np.array(plen) + j)
+        assert pages == 1 and items.max() == most and items.min() == 1, (pages, items)
     log(f"split merge at 8 rows: {kernel}")
     eng = _engine(s, wd, n, 4200, 4224, n * 67)
     r = teacher_forced_parity(eng, s, w64, wl, 3, 2e-2, 1.0, 6, check=[0, 2, n - 1])

@@ -6,12 +6,12 @@ up to 16,384 tokens.  These cases put the kernels there, depth-truncated so
 that the oracle (prefill in 2,048-token pieces) finishes in seconds:
 
 * decode at positions up to 17,407 (0.5B layer) and past 8k (7B layer),
-  where a row's context is split over 100-300 pieces and the 1024-thread
+  where a row's context is split over 91 and 44 items and the 1024-thread
   merge combines them;
-* a 33k-token context of an hd-64 model, whose 521 splits run the merge's
-  loop past its 512-entry LDS cache;
-* nine rows at the 7B layer (one at 17,400 tokens) whose splits fit the
+* a 33k-token context of an hd-64 model, split over 174 items;
+* nine rows at the 7B layer (one at 17,400 tokens) whose items fit the
   one-wave merge with two dimensions per lane;
+* sixteen rows of 6,600 and more tokens, whose items span more than 64 pages;
 * 512 live rows at the 7B layer (the MFMA-tiled decode GEMMs);
 * one prefill chunk of exactly 16,384 tokens at the 7B layer;
 * greedy agreement over 1,024 teacher-forced positions at the full
@@ -25,7 +25,7 @@ import dataclasses
 import numpy as np
 import pytest
 
-from tests.gpu_helpers import log, rp, teacher_forced_parity
+from tests.gpu_helpers import decode_items, log, rp, teacher_forced_parity
 from workloads import SHAPES, ModelShape, make_weights, make_workload, truncated, weights_to_numpy
 from workloads.gen import Workload
 
@@ -58,15 +58,6 @@ def _engine(shape, wdev, wl, n_new, max_prefill=8192, max_seqs=None):
                     max_context=max_ctx, kv_pages=pages)
 
 
-def _splits(shape, ctx):
-    """Decode-attention splits per row for these contexts (the engine's plan: as many
-    splits as fill 2048 waves over the KV heads, whole 64-token pages each)."""
-    pages = (np.asarray(ctx) + 63) // 64
-    target = max(1, 2048 // shape.n_kv)
-    pps = max(1, -(-int(pages.sum()) // target))
-    return -(-np.asarray(ctx) // (pps * 64))
-
-
 def _run(name, shape, wl, n_new, temp, check=None, max_prefill=8192, max_seqs=None, seed_w=0):
     log(f"{name}: weights, {wl.n} rows, prompts {sorted(wl.prompt_lens().tolist())[-3:]} (longest)")
     wd = make_weights(shape, seed=seed_w, device=DEV)
@@ -85,8 +76,8 @@ def test_decode_0p5b_layer_at_position_17407():
     s = truncated(SHAPES["qwen2.5-0.5b"], 1, vocab=4096)
     wl = _workload(s, [17380, 300, 45], seed=1)
     n_new = 28  # the long row's last position is 17,407
-    sp = _splits(s, wl.prompt_lens() + n_new - 1)
-    assert sp[0] >= 91, sp
+    _, items = decode_items(s, wl.prompt_lens() + n_new - 1)
+    assert items[0] >= 91, items
     _run("0.5b-L1 17k", s, wl, n_new, 1.0)
 
 
@@ -94,20 +85,20 @@ def test_decode_7b_layer_past_8k_thousand_thread_merge():
     s = truncated(SHAPES["qwen2.5-7b"], 1, vocab=4096)
     wl = _workload(s, [8300, 1500, 200], seed=2)
     n_new = 16
-    sp = _splits(s, wl.prompt_lens() + n_new - 1)
-    assert sp[0] >= 91 and wl.n < 8, sp  # fewer than 8 rows: the 1024-thread merge
+    _, items = decode_items(s, wl.prompt_lens() + n_new - 1)
+    assert items[0] >= 40 and wl.n < 8, items  # fewer than 8 rows: the 1024-thread merge
     _run("7b-L1 8k", s, wl, n_new, 1.0)
 
 
 HD64_NKV1 = ModelShape("hd64-nkv1", 1, 256, 4, 1, 64, 512, 2048, False, "bf16")
 
 
-def test_decode_hd64_beyond_the_merge_lds_cache():
+def test_decode_hd64_at_33k_tokens():
     s = HD64_NKV1
     wl = _workload(s, [33300, 700, 100], seed=3)
     n_new = 6
-    sp = _splits(s, wl.prompt_lens() + n_new - 1)
-    assert sp[0] > 512, sp  # splits past the merge's 512-entry LDS cache
+    _, items = decode_items(s, wl.prompt_lens() + n_new - 1)
+    assert items[0] > 128, items
     _run("hd64 33k", s, wl, n_new, 1.0)
 
 
@@ -116,9 +107,22 @@ def test_decode_7b_layer_nine_rows_one_wave_merge_with_a_17k_row():
     lens = [17400, 2000] + [16000] * 7
     wl = _workload(s, lens, seed=4)
     n_new = 8  # the 17,400-token row reaches position 17,407
-    sp = _splits(s, wl.prompt_lens() + n_new - 1)
-    assert wl.n >= 8 and sp.max() <= 64 and sp[1] >= 2, sp  # one wave per (row, head), hd 128
+    _, items = decode_items(s, wl.prompt_lens() + n_new - 1)
+    # one wave per (row, head), hd 128; a row of one item beside rows of several
+    assert wl.n >= 8 and 8 <= items.max() <= 64 and items[1] == 1 and items[2] > 1, items
     _run("7b-L1 nine rows", s, wl, n_new, 1.0, check=[0, 1], max_prefill=16384)
+
+
+def test_decode_items_of_more_than_64_pages():
+    """Sixteen rows whose items span 72 pages: the page ids past an item's 64th come from the page table
+    instead of the wave's lanes, in a row's first item and, at 9,000 tokens, in one that starts at page 72."""
+    s = ModelShape("hd64-nkv8", 1, 384, 8, 8, 64, 256, 640, False, "bf16")
+    wl = _workload(s, [6600] * 15 + [9000], seed=5)
+    n_new = 3
+    for j in range(1, n_new):
+        pages, items = decode_items(s, wl.prompt_lens() + j)
+        assert pages > 64 and items.tolist() == [2] * 16 and 9000 - 64 * pages > 64 * 64, (pages, items)
+    _run("hd64 long items", s, wl, n_new, 1.0, check=[0, 15], max_prefill=16384)
 
 
 def test_decode_512_rows_7b_layer():
