@@ -41,7 +41,7 @@ def deep_source_digest(root: str = ROOT) -> str:
     gemm = open(os.path.join(root, SOURCE)).read()
     plans = open(os.path.join(root, PLANS)).read()
     parts = [_between(gemm, "template <bool PACKED>\n__device__ __forceinline__ bf16x8_t load_w16", "\n}\n"),
-             _between(gemm, "template <int R, int MT, int D, bool SILU, bool PACKED>\n__global__ __launch_bounds__(256) "
+             _between(gemm, "template <int R, int D, bool SILU, bool PACKED>\n__global__ __launch_bounds__(256) "
                             "void k_gemm_deep", "\n}\n"),
              _between(gemm, "template <int R, int MT, bool SILU, bool PACKED>\n__global__ __launch_bounds__(256) "
                             "void k_gemm_ring", "\n}\n"),
@@ -56,8 +56,9 @@ SHAPE = {"H": 3584, "I": 18944}  # Qwen2.5-7B hidden and intermediate sizes
 
 def gate_up_tiles(name: str):
     """Activation tiles of a gate/up (SiLU) decode-GEMM instantiation, else None."""
-    m = (re.search(r"k_gemm_deep<(\d+), (\d+), (\d+), true(?:, (?:true|false))?>", name) or
-         re.search(r"k_gemm_ring<(\d+), (\d+), true, (?:true|false)>", name))
+    if re.search(r"k_gemm_deep<\d+, \d+, true, (?:true|false)>", name):
+        return 1
+    m = re.search(r"k_gemm_ring<(\d+), (\d+), true, (?:true|false)>", name)
     return int(m.group(2)) if m else None
 
 

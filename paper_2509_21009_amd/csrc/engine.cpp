@@ -88,8 +88,8 @@ ScratchPlan plan_scratch(const rp_model_config& c, const rp_engine_limits& l) {
   p.part_elems = std::max(static_cast<size_t>(l.max_prefill_tokens) * nmax,
                           static_cast<size_t>(kMaxGemmSplits) * l.max_seqs * nmax);
   const size_t T = l.max_prefill_tokens, S = l.max_seqs;
-  // decode: 7 ints per row + 1, padded to 16 bytes, then 4 per split; prefill: 3 per token + 8 per row + 1
-  p.meta_ints = static_cast<int32_t>(std::max(7 * S + 4 + 4 * static_cast<size_t>(p.split_cap), 3 * T + 8 * S + 1));
+  // decode: 6 ints per row + 1, padded to 16 bytes, then 4 per split; prefill: 3 per token + 8 per row + 1
+  p.meta_ints = static_cast<int32_t>(std::max(6 * S + 4 + 4 * static_cast<size_t>(p.split_cap), 3 * T + 8 * S + 1));
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += align256(bytes); return o; };
   p.x = take(mmax * H * 4);
@@ -566,7 +566,7 @@ void Engine::forward(int M, bool pre, int n_seq, int total_items, int total_spli
       aa.seq_ntok = m_seq_ntok_; aa.item_off = m_item_off_; aa.total_items = total_items;
       launch_timed(RP_K_ATTN, attn_bytes, attn_flops, [&] { return launch_attn_prefill(bf16_, aa, s); });
     } else {
-      aa.B = M; aa.row_slot = m_slot_; aa.row_ctx = m_ctx_; aa.split_off = m_split_off_;
+      aa.B = M; aa.split_off = m_split_off_;
       aa.total_splits = total_splits; aa.tokens_per_split = tps; aa.split_desc = m_split_desc_;
       aa.max_row_splits = max_row_splits_;
       aa.rope = ra;
@@ -842,14 +842,13 @@ int32_t Engine::decode_step(const int32_t* forced, float* logits_out, int64_t* r
     }
     if (total_splits > plan_.split_cap) throw RpError(RP_ERR_CAPACITY, "decode split capacity exceeded");
   }
-  const size_t desc_at = (7 * static_cast<size_t>(B) + 1 + 3) & ~static_cast<size_t>(3);
+  const size_t desc_at = (6 * static_cast<size_t>(B) + 1 + 3) & ~static_cast<size_t>(3);
   const size_t ints = desc_at + 4 * static_cast<size_t>(total_splits);
   int32_t* m = stage_meta(ints);
   int32_t* in_tok = m;
   int32_t* slot = in_tok + B;
   int32_t* pos = slot + B;
-  int32_t* ctx = pos + B;
-  int32_t* split_off = ctx + B;
+  int32_t* split_off = pos + B;
   int32_t* gen_pos = split_off + B + 1;
   int32_t* gen_hist = gen_pos + B;
   int32_t* desc = m + desc_at;
@@ -859,7 +858,6 @@ int32_t Engine::decode_step(const int32_t* forced, float* logits_out, int64_t* r
     in_tok[i] = forced ? forced[i] : -1;
     slot[i] = rows[i];
     pos[i] = q.prompt_len + q.n_gen - 1;
-    ctx[i] = pos[i] + 1;
     gen_pos[i] = pos[i] + 1;
     gen_hist[i] = q.n_gen;
     split_off[i] = sx;
@@ -901,8 +899,8 @@ int32_t Engine::decode_step(const int32_t* forced, float* logits_out, int64_t* r
   split_off[B] = total_splits;
   upload_meta(m, ints);
   const int32_t* d = d_meta_;
-  m_in_tok_ = d; m_slot_ = d + B; m_pos_ = d + 2 * B; m_ctx_ = d + 3 * B; m_split_off_ = d + 4 * B;
-  m_gen_pos_ = d + 5 * B + 1; m_gen_hist_ = d + 6 * B + 1; m_gen_slot_ = m_slot_;
+  m_in_tok_ = d; m_slot_ = d + B; m_pos_ = d + 2 * B; m_split_off_ = d + 3 * B;
+  m_gen_pos_ = d + 4 * B + 1; m_gen_hist_ = d + 5 * B + 1; m_gen_slot_ = m_slot_;
   m_split_desc_ = d + desc_at;
   TraceRec* tr = trace_cap_ ? trace_begin(0, B, sum_ctx_) : nullptr;
   forward(B, false, 0, 0, total_splits, tps);

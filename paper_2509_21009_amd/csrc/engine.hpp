@@ -282,7 +282,7 @@ class Engine {
   const int32_t* d_meta_ = nullptr;
   // metadata pointers used by forward()
   const int32_t *m_in_tok_ = nullptr, *m_slot_ = nullptr, *m_pos_ = nullptr, *m_hist_ = nullptr,
-                *m_ctx_ = nullptr, *m_split_off_ = nullptr, *m_seq_slot_ = nullptr,
+                *m_split_off_ = nullptr, *m_seq_slot_ = nullptr,
                 *m_seq_row0_ = nullptr, *m_seq_pos0_ = nullptr, *m_seq_ntok_ = nullptr,
                 *m_item_off_ = nullptr, *m_last_row_ = nullptr, *m_gen_pos_ = nullptr,
                 *m_gen_hist_ = nullptr, *m_gen_slot_ = nullptr, *m_split_desc_ = nullptr;

@@ -24,6 +24,7 @@
 // partial outputs of rows with more than one item.
 #include <type_traits>
 
+#include "decode_plan.hpp"
 #include "device_common.hpp"
 #include "kernels.hpp"
 #include "lds_dma.hpp"
@@ -34,15 +35,9 @@ namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
 
-// Token (within a 64-token page) that MFMA row i of S^T tile t stands for.
-__device__ __forceinline__ int tile_token(int t, int i) {
-  return 32 * (t >> 1) + 8 * (i >> 2) + 4 * (t & 1) + (i & 3);
-}
-
 struct SoftmaxState {
   float m, l;
 };
-
 
 // A 16-byte load marked non-temporal, for the KV cache that a decode step
 // streams exactly once: the caches then do not keep it at the expense of
@@ -343,17 +338,16 @@ __global__ __launch_bounds__(64 * kDecodeWaves, 2) void k_attn_decode_bf16(AttnA
 }
 
 // One block per (row, query head) with HD x 8 threads (rows with more than
-// one split): the splits' maxima
+// one split, and kMaxRowItems at most): the splits' maxima
 // and sums are staged in LDS, each of 8 thread groups accumulates every 8th
 // split for all HD output elements, and the groups are summed in LDS.  Long
 // contexts at small batch have hundreds of splits, which a single serial
 // loop per element would walk one memory latency at a time.
-constexpr int kMergeCache = 512;
 constexpr int kMergeGroups = 8;
 
 template <int HD>
 __global__ __launch_bounds__(HD * kMergeGroups) void k_attn_merge(AttnArgs a) {
-  __shared__ float sm[kMergeCache], sl[kMergeCache];
+  __shared__ float sm[kMaxRowItems], sl[kMaxRowItems];
   __shared__ float part_num[kMergeGroups][HD];
   __shared__ float part_den[kMergeGroups];
   __shared__ float wmax[HD * kMergeGroups / 64];
@@ -363,13 +357,13 @@ __global__ __launch_bounds__(HD * kMergeGroups) void k_attn_merge(AttnArgs a) {
   const int kh = h / G, c = h % G;
   const int s0 = a.split_off[b], n = a.split_off[b + 1] - s0;
   if (n <= 1) return;  // single-split rows were written by the decode kernel
-  const int nc = min(n, kMergeCache);
   auto m_of = [&](int t) { return a.part_ml[(static_cast<size_t>(s0 + t) * a.n_kv + kh) * 32 + c]; };
   auto l_of = [&](int t) { return a.part_ml[(static_cast<size_t>(s0 + t) * a.n_kv + kh) * 32 + 16 + c]; };
   float mx = -INFINITY;
   for (int t = threadIdx.x; t < n; t += blockDim.x) {
     const float mv = m_of(t);
-    if (t < nc) { sm[t] = mv; sl[t] = l_of(t); }
+    sm[t] = mv;
+    sl[t] = l_of(t);
     mx = fmaxf(mx, mv);
   }
   mx = wave_max(mx);
@@ -380,21 +374,15 @@ __global__ __launch_bounds__(HD * kMergeGroups) void k_attn_merge(AttnArgs a) {
   // Split weights into LDS first, so that the loop below issues nothing but
   // independent partial-output loads (unrolled 16 deep: a 256-split row takes
   // two memory round trips per thread instead of one per few splits).
-  for (int t = threadIdx.x; t < nc; t += blockDim.x) sm[t] = (sm[t] == -INFINITY) ? 0.f : exp2f(sm[t] - mx);
+  for (int t = threadIdx.x; t < n; t += blockDim.x) sm[t] = (sm[t] == -INFINITY) ? 0.f : exp2f(sm[t] - mx);
   __syncthreads();
   const float* po = a.part_o + (static_cast<size_t>(s0) * a.n_kv + kh) * 16 * HD + c * HD + d;
   const size_t po_stride = static_cast<size_t>(a.n_kv) * 16 * HD;  // one split
   float num = 0.f, den = 0.f;
 #pragma unroll 16
-  for (int t = q; t < nc; t += kMergeGroups) num += sm[t] * po[t * po_stride];
+  for (int t = q; t < n; t += kMergeGroups) num += sm[t] * po[t * po_stride];
   if (d == 0)
-    for (int t = q; t < nc; t += kMergeGroups) den += sm[t] * sl[t];
-  for (int t = nc + q; t < n; t += kMergeGroups) {  // splits beyond the LDS cache
-    const float ms = m_of(t);
-    const float w = (ms == -INFINITY) ? 0.f : exp2f(ms - mx);
-    num += w * po[t * po_stride];
-    if (d == 0) den += w * l_of(t);
-  }
+    for (int t = q; t < n; t += kMergeGroups) den += sm[t] * sl[t];
   part_num[q][d] = num;
   if (d == 0) part_den[q] = den;
   __syncthreads();
@@ -834,10 +822,11 @@ hipError_t launch_attn_decode(int bf16, const AttnArgs& a, hipStream_t s) {
 
 hipError_t launch_attn_merge(const AttnArgs& a, hipStream_t s) {
   if (a.B <= 0) return hipSuccess;
+  if (a.max_row_splits < 1 || a.max_row_splits > kMaxRowItems) return hipErrorInvalidValue;
   dim3 grid(a.B, a.n_q);
   // One wave per (row, head) pays off once there are many rows: at 64 rows of 8 splits it takes
   // 4.0 us against 9.6 us; at a single row the 1024-thread blocks are 0.3-1.3 us faster.
-  if (a.B >= 8 && a.max_row_splits >= 1 && a.max_row_splits <= kMergeFew) {
+  if (a.B >= 8 && a.max_row_splits <= kMergeFew) {
     if (a.hd != 128 && a.hd != 64) return hipErrorInvalidValue;
 #define RP_MERGE_FEW(NMAX)                                                                    \
     if (a.max_row_splits <= NMAX) {                                                           \

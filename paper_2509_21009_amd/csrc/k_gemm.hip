@@ -85,11 +85,10 @@ __device__ __forceinline__ bf16x8_t load_w16(__amdgpu_buffer_rsrc_t r, int off) 
   return __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, PACKED ? 2 : 0));
 }
 
-template <int R, int MT, int D, bool SILU, bool PACKED>
+template <int R, int D, bool SILU, bool PACKED>
 __global__ __launch_bounds__(256) void k_gemm_deep(GemmArgs a, int units_per_split) {
   static_assert(!SILU || R % 2 == 0, "SiLU pairs gate and up fragments");
-  constexpr int NACC = R * MT;
-  __shared__ __attribute__((aligned(16))) f32x4_t red[3][NACC][64];
+  __shared__ __attribute__((aligned(16))) f32x4_t red[3][R][64];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, r = lane & 15;
@@ -128,21 +127,17 @@ __global__ __launch_bounds__(256) void k_gemm_deep(GemmArgs a, int units_per_spl
   // apart; packed: the unit's 2 KB run, the lane's 16 bytes in each 1 KB half
   const int woff = PACKED ? (u0 + wave) * 2048 + lane * 16 : r * static_cast<int>(row_bytes) + kb;
   constexpr int kWStep = PACKED ? 4 * 2048 : 4 * 128, kWHalf = PACKED ? 1024 : 16;
-  int aoff[MT];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) aoff[mt] = (mt * 16 + r) * static_cast<int>(a.lda) * 2 + kb;
+  const int aoff = r * static_cast<int>(a.lda) * 2 + kb;
 
-  f32x4_t acc[R][MT];
+  f32x4_t acc[R];
 #pragma unroll
-  for (int t = 0; t < R; ++t)
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[t][mt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < R; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   // Weights: a ring of D stages.  Activations: one buffer, loaded one stage
   // ahead, after the weights of the current stage and before those of later
   // stages; vector loads complete in issue order, so waiting for the
   // activations of stage s never waits for weights of later stages.
-  bf16x8_t wv[D][R][2], av[MT][2];
+  bf16x8_t wv[D][R][2], av[2];
   auto load_w = [&](int s, int unit) {
     const int o = unit * kWStep;
 #pragma unroll
@@ -153,19 +148,14 @@ __global__ __launch_bounds__(256) void k_gemm_deep(GemmArgs a, int units_per_spl
   };
   auto load_a = [&](int unit) {
     const int o = unit * 512;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      av[mt][0] = load_bf16x8(ra, aoff[mt] + o);
-      av[mt][1] = load_bf16x8(ra, aoff[mt] + o + 16);
-    }
+    av[0] = load_bf16x8(ra, aoff + o);
+    av[1] = load_bf16x8(ra, aoff + o + 16);
   };
   auto compute = [&](int s) {
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int t = 0; t < R; ++t)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[t][mt] = mfma16x16x32(wv[s][t][j], av[mt][j], acc[t][mt]);
+      for (int t = 0; t < R; ++t) acc[t] = mfma16x16x32(wv[s][t][j], av[j], acc[t]);
   };
 
   // The prologue loads unconditionally (stages past the wave's range are
@@ -207,43 +197,34 @@ __global__ __launch_bounds__(256) void k_gemm_deep(GemmArgs a, int units_per_spl
 
   if (wave > 0) {
 #pragma unroll
-    for (int t = 0; t < R; ++t)
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) red[wave - 1][t * MT + mt][lane] = acc[t][mt];
+    for (int t = 0; t < R; ++t) red[wave - 1][t][lane] = acc[t];
   }
   __syncthreads();
   if (wave > 0) return;
 #pragma unroll
-  for (int t = 0; t < R; ++t)
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-      acc[t][mt] = acc[t][mt] + red[0][t * MT + mt][lane] + red[1][t * MT + mt][lane] + red[2][t * MT + mt][lane];
+  for (int t = 0; t < R; ++t) acc[t] = acc[t] + red[0][t][lane] + red[1][t][lane] + red[2][t][lane];
 
-  // lane (g, r) holds C^T[row base + t*16 + 4g + e][m = mt*16 + r]
+  // lane (g, r) holds C^T[row base + t*16 + 4g + e][m = r]
+  if (r >= a.M) return;
+  if (SILU) {
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
-    const int m = mt * 16 + r;
-    if (m >= a.M) continue;
-    if (SILU) {
+    for (int t = 0; t < R / 2; ++t) {
+      const int i0 = (blockIdx.x * (R / 2) + t) * 16 + g * 4;
+      if (i0 >= a.N) continue;
+      const f32x4_t gv = acc[t], uv = acc[t + R / 2];
+      uint2 pk;
+      pk.x = static_cast<uint32_t>(f32_to_bf16(silu(gv[0]) * uv[0])) |
+             (static_cast<uint32_t>(f32_to_bf16(silu(gv[1]) * uv[1])) << 16);
+      pk.y = static_cast<uint32_t>(f32_to_bf16(silu(gv[2]) * uv[2])) |
+             (static_cast<uint32_t>(f32_to_bf16(silu(gv[3]) * uv[3])) << 16);
+      *reinterpret_cast<uint2*>(static_cast<bf16_t*>(a.act_out) + static_cast<size_t>(r) * a.N + i0) = pk;
+    }
+  } else {
 #pragma unroll
-      for (int t = 0; t < R / 2; ++t) {
-        const int i0 = (blockIdx.x * (R / 2) + t) * 16 + g * 4;
-        if (i0 >= a.N) continue;
-        const f32x4_t gv = acc[t][mt], uv = acc[t + R / 2][mt];
-        uint2 pk;
-        pk.x = static_cast<uint32_t>(f32_to_bf16(silu(gv[0]) * uv[0])) |
-               (static_cast<uint32_t>(f32_to_bf16(silu(gv[1]) * uv[1])) << 16);
-        pk.y = static_cast<uint32_t>(f32_to_bf16(silu(gv[2]) * uv[2])) |
-               (static_cast<uint32_t>(f32_to_bf16(silu(gv[3]) * uv[3])) << 16);
-        *reinterpret_cast<uint2*>(static_cast<bf16_t*>(a.act_out) + static_cast<size_t>(m) * a.N + i0) = pk;
-      }
-    } else {
-#pragma unroll
-      for (int t = 0; t < R; ++t) {
-        const int n = (blockIdx.x * R + t) * 16 + g * 4;
-        if (n >= a.N) continue;
-        *reinterpret_cast<f32x4_t*>(a.part + (static_cast<size_t>(blockIdx.y) * a.M + m) * a.N + n) = acc[t][mt];
-      }
+    for (int t = 0; t < R; ++t) {
+      const int n = (blockIdx.x * R + t) * 16 + g * 4;
+      if (n >= a.N) continue;
+      *reinterpret_cast<f32x4_t*>(a.part + (static_cast<size_t>(blockIdx.y) * a.M + r) * a.N + n) = acc[t];
     }
   }
 }
@@ -795,9 +776,9 @@ void launch_deep_t(const GemmArgs& a, hipStream_t s) {
   const int per = SILU ? R / 2 : R;
   const int nb = (a.N / 16 + per - 1) / per;
   if (a.Wp.n_seg > 0)
-    launch_kernel((k_gemm_deep<R, 1, D, SILU, true>), dim3(nb, a.splits), dim3(256), 0, s, a, ups);
+    launch_kernel((k_gemm_deep<R, D, SILU, true>), dim3(nb, a.splits), dim3(256), 0, s, a, ups);
   else
-    launch_kernel((k_gemm_deep<R, 1, D, SILU, false>), dim3(nb, a.splits), dim3(256), 0, s, a, ups);
+    launch_kernel((k_gemm_deep<R, D, SILU, false>), dim3(nb, a.splits), dim3(256), 0, s, a, ups);
 }
 
 template <int R, int MT, bool SILU>

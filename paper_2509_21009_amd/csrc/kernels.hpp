@@ -123,7 +123,7 @@ struct RopeArgs {
 hipError_t launch_rope_append(int bf16, const RopeArgs& a, hipStream_t s);
 
 struct AttnArgs {
-  const void* q;                  // [rows, n_q, hd]
+  const void* q;                  // [rows, n_q, hd] (not read by the bf16 decode, which rotates its own from rope.part)
   const void* k_pool; const void* v_pool;
   const int32_t* page_table; int32_t pt_stride;
   int n_q, n_kv, hd;
@@ -131,9 +131,9 @@ struct AttnArgs {
   // fp32 model: one query row per (token, head), keys 0..tok_pos[row]
   int n_rows; const int32_t* tok_slot; const int32_t* tok_pos;
   // decode (one query token per sequence, split over the context):
-  int B; const int32_t* row_slot; const int32_t* row_ctx; const int32_t* split_off;
+  int B; const int32_t* split_off;
   int total_splits; int tokens_per_split;
-  int max_row_splits;             // most splits of any row (0: unknown); picks the merge kernel
+  int max_row_splits;             // most splits of any row; picks the merge kernel
   // [total_splits, 4]: row (+ 2^30 if its only split, + 2^29 if it holds the row's newest token), first
   // and end cached key, slot; the longest first
   const int32_t* split_desc;

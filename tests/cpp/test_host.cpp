@@ -154,7 +154,10 @@ static void test_decode_items_fit() {
     const int64_t pps = rollpack::decode_pages_per_item(n_kv, hd, total, longest, B);
     CHECK(pps >= 1);
     int64_t items = 0;
-    for (int64_t p : pages) items += (p + pps - 1) / pps;
+    for (int64_t p : pages) {
+      CHECK((p + pps - 1) / pps <= rollpack::kMaxRowItems);
+      items += (p + pps - 1) / pps;
+    }
     CHECK(items <= rollpack::decode_split_target(n_kv) + B);
   }
 }
