@@ -459,9 +459,9 @@ typedef enum rp_kernel_class {
   RP_K_EMBED_NORM = 0,   /* embedding gather + first RMSNorm */
   RP_K_ADD_NORM = 1,     /* residual add of split-K partials + RMSNorm */
   RP_K_GEMM_QKV = 2,
-  RP_K_ROPE_APPEND = 3,  /* q/k/v bias + RoPE + paged KV append */
-  RP_K_ATTN = 4,         /* prefill or decode attention */
-  RP_K_ATTN_MERGE = 5,   /* decode split merge */
+  RP_K_ROPE_APPEND = 3,  /* q/k/v bias + RoPE + paged KV append (not in bf16 decode steps) */
+  RP_K_ATTN = 4,         /* prefill or decode attention; in bf16 decode steps with the work of RP_K_ROPE_APPEND */
+  RP_K_ATTN_MERGE = 5,   /* decode split merge, in steps where some row has more than one split */
   RP_K_GEMM_O = 6,
   RP_K_GEMM_GATE_UP = 7, /* with the SiLU * up epilogue */
   RP_K_GEMM_DOWN = 8,

@@ -534,7 +534,9 @@ void Engine::forward(int M, bool pre, int n_seq, int total_items, int total_spli
     attn_bytes = Md * kv_tok_bytes + 2.0 * Md * nq * hd * e;
     attn_flops = 2.0 * nq * hd * sum_ctx_sq_;
   } else {
-    attn_bytes = sum_ctx_ * kv_tok_bytes + 2.0 * Md * nq * hd * e;
+    // K/V of every attended token (the newest one's written instead of read), and the queries: the bf16 kernel forms
+    // them, and the newest K/V, from the projection's partials
+    attn_bytes = sum_ctx_ * kv_tok_bytes + (bf16_ ? Md * (nqkv_ * 4.0 + nq * hd * e) : 2.0 * Md * nq * hd * e);
     attn_flops = 4.0 * nq * hd * sum_ctx_;
   }
   for (int l = 0; l < cfg_.n_layers; ++l) {

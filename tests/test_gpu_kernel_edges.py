@@ -10,7 +10,7 @@ import numpy as np
 import pytest
 
 from oracle import model as om
-from tests.gpu_helpers import rp, teacher_forced_parity
+from tests.gpu_helpers import decode_items, rp, teacher_forced_parity
 from workloads import ModelShape, make_weights, weights_to_numpy
 from workloads.gen import Workload
 
@@ -165,3 +165,26 @@ def test_tiled_gemm_of_more_than_two_million_columns():
         err = (whole[lo:lo + 64] - part).abs().amax(1) / part.abs().amax(1)
         assert float(err.max()) <= 4e-2, (lo, err)
     eng.close()
+
+
+def test_decode_attention_profile_counts_its_fused_work():
+    """bf16 decode steps launch no rotation or append of their own: the attention class carries their
+    bytes, the projection's fp32 partials and the K/V of the cached and the new tokens, beside its output; a merge
+    is there only where some row has several items."""
+    wd = make_weights(SMALL, seed=3, device=DEV)
+    R = rp()
+    for plens, merges in (([5, 9, 70], 0), ([3000, 9], 1)):
+        wl = _workload(SMALL, plens, 1)
+        n = len(plens)
+        eng = R.Engine(SMALL, R.weights_for_engine(wd), max_seqs=n, max_prefill_tokens=4096, max_context=max(plens) + 4,
+                       kv_pages=sum(p // 64 + 1 for p in plens))
+        eng.prefill(wl.seq_ids, wl.prompt_tokens, wl.prompt_offsets, np.full(n, 3, np.int32), 1, 1.0)
+        eng.profile(["rope_append", "attn", "attn_merge"], every=1)
+        eng.decode_step()
+        got = {r["kernel"]: r for r in eng.profile_read()}
+        eng.close()
+        assert (decode_items(SMALL, np.array(plens) + 1)[1].max() > 1) == bool(merges)
+        assert "rope_append" not in got and got.get("attn_merge", {"launches": 0})["launches"] == merges
+        kv = 2 * SMALL.n_kv * SMALL.head_dim * 2 * sum(p + 1 for p in plens)
+        out = n * SMALL.n_q * SMALL.head_dim * 2
+        assert got["attn"]["bytes"] == kv + n * SMALL.qkv_out * 4 + out, got
