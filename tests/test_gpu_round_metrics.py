@@ -8,7 +8,10 @@ end time from the round's start (end_ms); a sequence of max_new = L finishes
 at the end of the step that produced its last token: the prefill chunk for
 L = 1, else decode step L - 1.  Those, and the makespan, recompute both
 metrics; the engine's own figures must agree to within the event timing
-resolution (a few microseconds per departure).  The same trace also fixes
+resolution (a few microseconds per departure).  The engine stamps a departure
+between the end of the step that finished it and the start of the next one: what
+the device waited there for the host, start_(k+1) - end_k from the same trace, is
+added to the bar.  The same trace also fixes
 prefill_ms (the end of the last prefill chunk) and the decode-step count.
 """
 import numpy as np
@@ -35,13 +38,17 @@ def _check_round(st, rec, max_new):
     assert np.all(dec["rows"] == [int(np.sum(max_new > j)) for j in range(1, int(max_new.max()))])
     f = np.where(max_new == 1, pre["end_ms"][-1], dec["end_ms"][np.maximum(max_new, 2) - 2])
     idle_ref = float(np.sum(T - f)) * 1e-3
+    # what the device waited for the host after each step (after the last: until the round's end)
+    wait = np.maximum(np.append(rec["end_ms"][1:] - rec["ms"][1:], T) - rec["end_ms"], 0.0)
+    wait_pre, wait_dec = wait[rec["kind"] == 1][-1], wait[rec["kind"] == 0]
+    wait_s = float(np.sum(np.where(max_new == 1, wait_pre, wait_dec[np.maximum(max_new, 2) - 2]))) * 1e-3
     slot_ref = idle_ref / (len(max_new) * T * 1e-3)
     log(f"  makespan {T:.3f} ms, idle {st['idle_slot_s']:.6f} s (recomputed {idle_ref:.6f}), "
-        f"slot_idle {st['slot_idle']:.5f} (recomputed {slot_ref:.5f})")
-    tol_s = len(max_new) * 20e-6 + 1e-3 * idle_ref
+        f"slot_idle {st['slot_idle']:.5f} (recomputed {slot_ref:.5f}), device waits at departures {wait_s:.6f} s")
+    tol_s = len(max_new) * 20e-6 + 1e-3 * idle_ref + wait_s
     assert abs(st["idle_slot_s"] - idle_ref) <= tol_s
     assert abs(st["slot_idle"] - slot_ref) <= tol_s / (len(max_new) * T * 1e-3)
-    assert abs(st["prefill_ms"] - pre["end_ms"][-1]) <= 0.02 + 1e-3 * st["prefill_ms"]
+    assert abs(st["prefill_ms"] - pre["end_ms"][-1]) <= 0.02 + 1e-3 * st["prefill_ms"] + wait_pre
     assert T >= dec["end_ms"][-1] and T - dec["end_ms"][-1] <= 0.05 * T + 1.0
 
 
