@@ -105,16 +105,20 @@ __global__ __launch_bounds__(1024) void k_embed_norm(EmbedArgs a) {
   norm_store<T>(xv, gv, a.H, a.eps, static_cast<T*>(a.h) + static_cast<size_t>(i) * a.H, red);
 }
 
-template <typename T, int S>
-__global__ __launch_bounds__(1024) void k_add_rmsnorm(AddNormArgs a) {
+// THREADS: 1024, whose registers hold the row, its gains and up to 13 partials of it; or 512, for rows of at
+// most 4,096 elements, which hold 16.  (With 1,024 threads 14-16 partials and the gains spilled: 7.2 us at
+// 65 rows of H = 896 against 4.5.)
+template <typename T, int S, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_add_rmsnorm(AddNormArgs a) {
   __shared__ float red[16];
   const int i = blockIdx.x;
   float* x = a.x + static_cast<size_t>(i) * a.H;
   const int nc = a.H / 4;
   const size_t plane = static_cast<size_t>(a.M) * a.H;
   float4 xv[kRowChunks];
+  constexpr bool kEarlyGains = S <= 13 || THREADS <= 512;
   float4 pv[S > 0 ? S : 1][kRowChunks], gv[kRowChunks];
-  load_gains(static_cast<const T*>(a.norm_g), a.H, gv);
+  if (kEarlyGains) load_gains(static_cast<const T*>(a.norm_g), a.H, gv);
 #pragma unroll
   for (int v = 0; v < kRowChunks; ++v) {
     const int c = threadIdx.x + v * blockDim.x;
@@ -138,6 +142,7 @@ __global__ __launch_bounds__(1024) void k_add_rmsnorm(AddNormArgs a) {
       }
     }
   }
+  if (!kEarlyGains) load_gains(static_cast<const T*>(a.norm_g), a.H, gv);
   norm_store<T>(xv, gv, a.H, a.eps, static_cast<T*>(a.h) + static_cast<size_t>(i) * a.H, red);
 }
 
@@ -182,28 +187,27 @@ __global__ __launch_bounds__(256) void k_rope_append(RopeArgs a) {
 // The bf16 prefill's bias, RoPE and append, 16 bytes of partials at a time.  The first blocks take the
 // q and k pairs, four consecutive dimension pairs per thread.  The rest take 64 tokens x 64 value
 // dimensions each and turn them through LDS: a V page holds a dimension's 32 tokens side by side, so
-// lanes store along tokens (64-byte runs) instead of 2 bytes per cache line.  ONE: a single partial.
+// lanes store along tokens (64-byte runs) instead of 2 bytes per cache line.  The S partials are all loaded
+// before the first is added (one after the other, seven of them took 7.5 us at 65 tokens against 3.8).
 // 11,500 tokens of the 7B shape: 66 us (4.6 TB/s) against 140 for one pair or value per thread; 9,216 tokens of
 // the 0.5B 14.6 against 24.8 us.
 constexpr int kRopeTok = 64, kRopeDim = 64;
 
-template <bool ONE>
+template <int S>
 __global__ __launch_bounds__(256) void k_rope_prefill(RopeArgs a, int qk_blocks_per_row) {
   __shared__ bf16_t sv[kRopeDim][kRopeTok + 2];
   const int hd = a.hd, half = hd / 2;
   const int nq_el = a.n_q * hd, nk_el = a.n_kv * hd, nqkv = nq_el + 2 * nk_el;
   const size_t plane = static_cast<size_t>(a.M) * nqkv;
-  const int S = ONE ? 1 : a.splits;
   auto sum4 = [&](const float* p) {
-    float4 u = *reinterpret_cast<const float4*>(p);
-    if (!ONE) {
-#pragma unroll 4
-      for (int s = 1; s < S; ++s) {
-        const float4 w = *reinterpret_cast<const float4*>(p + s * plane);
-        u.x += w.x; u.y += w.y; u.z += w.z; u.w += w.w;
-      }
+    float4 w[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) w[s] = *reinterpret_cast<const float4*>(p + s * plane);
+#pragma unroll
+    for (int s = 1; s < S; ++s) {
+      w[0].x += w[s].x; w[0].y += w[s].y; w[0].z += w[s].z; w[0].w += w[s].w;
     }
-    return u;
+    return w[0];
   };
   const int n_qk = a.M * qk_blocks_per_row;
   if (static_cast<int>(blockIdx.x) < n_qk) {
@@ -444,7 +448,8 @@ int row_threads(int H) {
 
 template <typename T, int S>
 void launch_add_norm_s(const AddNormArgs& a, int threads, hipStream_t s) {
-  launch_kernel((k_add_rmsnorm<T, S>), dim3(a.M), dim3(threads), 0, s, a);
+  if (S > 13 && threads <= 512) launch_kernel((k_add_rmsnorm<T, S, (S > 13 ? 512 : 1024)>), dim3(a.M), dim3(threads), 0, s, a);
+  else launch_kernel((k_add_rmsnorm<T, S, 1024>), dim3(a.M), dim3(threads), 0, s, a);
 }
 
 template <typename T>
@@ -484,12 +489,17 @@ hipError_t launch_rope_f32(const RopeArgs& a, hipStream_t s) {
 
 // bf16 prefill.  Partials, tables and pools are 256-byte aligned parts of the engine's workspaces.
 hipError_t launch_rope_bf16(const RopeArgs& a, hipStream_t s) {
-  if (a.hd % kRopeDim || a.splits < 1) return hipErrorInvalidValue;
+  if (a.hd % kRopeDim) return hipErrorInvalidValue;
   const int per_row = ((a.n_q + a.n_kv) * (a.hd / 8) + 255) / 256;
   const int v_blocks = (a.M + kRopeTok - 1) / kRopeTok * (a.n_kv * a.hd / kRopeDim);
   const dim3 grid(a.M * per_row + v_blocks);
-  if (a.splits == 1) launch_kernel(k_rope_prefill<true>, grid, dim3(256), 0, s, a, per_row);
-  else launch_kernel(k_rope_prefill<false>, grid, dim3(256), 0, s, a, per_row);
+  switch (a.splits) {
+#define RP_ROPE(S) case S: launch_kernel(k_rope_prefill<S>, grid, dim3(256), 0, s, a, per_row); break;
+    RP_ROPE(1) RP_ROPE(2) RP_ROPE(3) RP_ROPE(4) RP_ROPE(5) RP_ROPE(6) RP_ROPE(7) RP_ROPE(8)
+    RP_ROPE(9) RP_ROPE(10) RP_ROPE(11) RP_ROPE(12) RP_ROPE(13) RP_ROPE(14) RP_ROPE(15) RP_ROPE(16)
+#undef RP_ROPE
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 }  // namespace

@@ -39,3 +39,18 @@ def test_m0_wait_state_before_loads_to_lds(tmp_path):
     for i in loads:
         assert not re.match(r"s_\w+ m0,", code[i - 1]), code[i - 2:i + 1]
         assert any(re.match(r"s_\w+ m0,", t) for t in code[i - 3:i - 1]), code[i - 3:i + 1]
+
+
+@pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="no hipcc")
+def test_row_kernels_keep_their_partials_in_registers():
+    """The row kernels load every split's partials before they add the first.  None spills, but for the
+    residual norm of rows of more than 4,096 elements with 15 or 16 partials, which 128 registers do not hold."""
+    asm = subprocess.run([build.HIPCC, *build.COMMON, *build.DEVICE, "--cuda-device-only", "-S",
+                          os.path.join(build.CSRC, "k_elementwise.hip"), "-o", "-"],
+                         check=True, capture_output=True, text=True, timeout=300).stdout
+    scratch = {m.group(1): int(m.group(2)) for m in
+               re.finditer(r"^(_Z\w+):.*?; ScratchSize: (\d+)", asm, flags=re.S | re.M)}
+    assert any("k_rope_prefill" in k for k in scratch)
+    spilled = {k for k, v in scratch.items() if v > 0}
+    wide = {k for k in scratch if re.search(r"k_add_rmsnormI[tf]Li1[56]ELi1024E", k)}
+    assert len(wide) == 4 and spilled <= wide, spilled - wide
