@@ -1,6 +1,6 @@
 // Causal GQA attention over the paged KV cache.
 //
-// Decode: a block of four waves owns a work item: the G query heads of a token
+// Decode: a block of four waves (or one) owns a work item: the G query heads of a token
 // (up to 16 query rows that share one KV head) and a range of KV tokens, whose
 // half pages its waves take in turn.  Per 32-token half page a wave computes
 // S^T = K Q^T as two 16x16 MFMA tiles, runs an online softmax in the log2
@@ -57,7 +57,7 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_hw{lo, hi}, bf16x2_hw));
 }
 
-// Decode attention of one work item: (row, KV head, range of cached keys), one block of 4 waves.
+// Decode attention of one work item: (row, KV head, range of cached keys), one block of NW waves, 4 or 1.
 // The block sums the q/k/v projection's split partials of its G query heads itself, adds the
 // bias and rotates them into LDS, while its first K/V loads are already in flight; the item with
 // the row's newest token does the same for that token's K and V, appends them to the cache and
@@ -69,11 +69,14 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 // rows of 200-1,700 tokens at the 7B layer stream 5.4 TB/s, 118 us against 148 for one-wave items with
 // rotation, append and merge launches; 256 rows at the 0.5B layer 22 against 32 us; by latency at few
 // (one row of 12k tokens: 10 + 6 us with its merge against 20).
-constexpr int kDecodeWaves = 4;
-
-template <int HD>
-__global__ __launch_bounds__(64 * kDecodeWaves, 2) void k_attn_decode_bf16(AttnArgs a) {
-  constexpr int KS = HD / 32, NB = HD / 16, D = 2, NW = kDecodeWaves, HALF = HD / 2;
+// A block of four waves takes about 10 us from its start to its first MFMA and through its end whatever its length,
+// and two fit a CU.  Where items are many and short those ends would run in many rounds: such steps run one wave
+// per item, eight to a CU, whose ends overlap (512 rows of 60 tokens at the 7B layer 35 us against 47, at
+// the 32B layer 61 against 79; 512 of 350-1,050 tokens 141 against 144 and 278 against 289; 16 KV heads without
+// groups, 128 rows of 2,000 tokens 345 against 374).
+template <int HD, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void k_attn_decode_bf16(AttnArgs a) {
+  constexpr int KS = HD / 32, NB = HD / 16, D = 2, HALF = HD / 2;
   constexpr int OLD = HD + 4;  // padded row of the waves' outputs (floats)
   __shared__ __attribute__((aligned(16))) bf16_t sq[16 * HD], snk[HD], snv[HD];
   __shared__ __attribute__((aligned(16))) float so[NW][16 * OLD];
@@ -813,10 +816,18 @@ hipError_t launch_attn_decode(int bf16, const AttnArgs& a, hipStream_t s) {
   }
   if (a.B <= 0 || a.total_splits <= 0) return hipSuccess;
   if (a.n_q / a.n_kv > 16 || a.tokens_per_split % kPageTokens != 0 || !a.split_desc) return hipErrorInvalidValue;
-  dim3 grid(a.total_splits * a.n_kv);
-  if (a.hd == 128) launch_kernel(k_attn_decode_bf16<128>, grid, dim3(64 * kDecodeWaves), 0, s, a);
-  else if (a.hd == 64) launch_kernel(k_attn_decode_bf16<64>, grid, dim3(64 * kDecodeWaves), 0, s, a);
-  else return hipErrorInvalidValue;
+  if (a.hd != 128 && a.hd != 64) return hipErrorInvalidValue;
+  const dim3 grid(a.total_splits * a.n_kv);
+  // One wave per item from 2,048 items of at most 32 pages on: one round of eight waves per CU, or more.  Below that
+  // four waves are as fast or faster (1,320 items of the 7B layer at 330 rows 117 against 119 us, 1,024 of the 0.5B
+  // layer at 512 rows 39 against 42), and at 63 pages, too (2,048 items 670 against 696).
+  if (static_cast<int>(grid.x) >= 2048 && a.tokens_per_split <= 32 * kPageTokens) {
+    if (a.hd == 128) launch_kernel((k_attn_decode_bf16<128, 1>), grid, dim3(64), 0, s, a);
+    else launch_kernel((k_attn_decode_bf16<64, 1>), grid, dim3(64), 0, s, a);
+  } else {
+    if (a.hd == 128) launch_kernel((k_attn_decode_bf16<128, 4>), grid, dim3(256), 0, s, a);
+    else launch_kernel((k_attn_decode_bf16<64, 4>), grid, dim3(256), 0, s, a);
+  }
   return hipGetLastError();
 }
 

@@ -77,6 +77,9 @@ def test_fp32_model_edges(hd, inter, vocab, plens):
     (3, 3, 128, [130, 2]),                                             # one query head per KV head
     (14, 2, 64, [2300] + [5, 64] * 3),                                 # a long row in items beside single ones
     (4, 4, 128, [1500, 1400, 63]),                                     # few rows: items and the 1024-thread merge
+    (16, 16, 64, [1, 31, 32, 33, 63, 64, 65, 127, 128, 129] * 13),     # 2,080 short items: one wave each
+    (12, 12, 128, [1, 31, 32, 33, 63, 64, 65, 130, 200] * 19),         # 2,052 of them at head dim 128
+    (16, 16, 64, [2100] + [40] * 127),                                 # 2,096, one row of four items
 ])
 def test_decode_attention_edges(n_q, n_kv, hd, plens):
     """Decode attention items: cached keys ending on and beside half pages and pages (the newest
