@@ -100,13 +100,18 @@ inline GemmPlan plan_ring(int M, int N, int K, bool silu, int split_lo, int spli
 }
 
 // k_gemm_tiled plan: the block tile (BM activation rows x BN weight rows) and
-// the K split, each tile shape and split in [split_lo, split_hi] priced in us as
+// the K split, each tile shape and split in [split_lo, split_hi] priced as
 // rounds of 256 blocks (one per CU) x (a start and an end + K steps of a block
-// x the tile's time per step), plus the fp32 partials the split writes and its
+// x the tile's price per step), plus the fp32 partials the split writes and its
 // consumer reads.  128 x 128 tiles run two blocks per CU, alone when the last
-// round has no more than one block per CU.  Fitted to a sweep of all tile shapes
-// and splits 1-16 at 70-9,216 rows of the 7B, 0.5B and 32B projections: the
-// plans are 1.0% from the fastest in the geometric mean and at most 8%.
+// round has no more than one block per CU.  Fitted to a sweep of single
+// launches, all tile shapes and splits 1-16 at 70-9,216 rows of the 7B, 0.5B and 32B
+// projections: the plans are 1.0% from the fastest in the geometric mean and at most 8%.
+// The prices rank plans; they are not the times of launches in a step, at the clock that
+// the chip holds there and with cold weights: 7B gate/up at 9,216 rows is priced at 1,313
+// and takes 1,937 us, at 397 rows 97 and 128-132, 0.5B gate/up at 256 rows 8.8 and
+// 13.4.  Partials and the second launch below are in us, so that beside them the
+// products count 1.3-1.7 times too little.
 // An unsplit product may run as two launches: the columns that fill whole rounds
 // of 256 x 256 tiles, and the rest in the tile that is fastest for them, instead
 // of a nearly empty last round (7B gate/up at 257-512 rows is 296 tiles on 256
@@ -162,6 +167,10 @@ inline GemmPlan plan_tiled(int M, int N, int K, bool silu, int split_lo, int spl
 //    takes 47.6 against 61.9 us for the register ring, the 0.5B head 78.7
 //    against 111 us, the 0.5B q/k/v and o 5.2 against 9.8 us for the streaming
 //    kernels; at 17-32 rows the gains are 0-10% at 7B and 40% at 0.5B.
+//  * with row-major weights the same kernels: four layers of the 0.5B take 151 us at
+//    one row and 185 at 64 against 174 and 290 for the kernels before the ring, of
+//    the 7B 489 and 586 against 520 and 780, two of the 32B 446 and 520 against 457
+//    and 706; no row count from 1 to 64 is slower.
 //  * up to 16 rows: the ring for products under 14M weights: alone and with
 //    warm weights it ties with kernels that stream weights and activations
 //    straight into registers, but within a step, whose weights come from HBM

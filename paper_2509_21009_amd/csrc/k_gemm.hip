@@ -249,7 +249,7 @@ template <int R, int MT, bool SILU, bool PACKED>
 __global__ __launch_bounds__(256) void k_gemm_ring(GemmArgs a, int units_per_split) {
   static_assert(R % 2 == 0, "register buffers alternate by fragment; SiLU pairs gate and up fragments");
   constexpr int WAVE_LDS = 40960, A_UNIT = MT * 2048, SLOTS = (WAVE_LDS - 2 * A_UNIT) / 2048;
-  static_assert(SLOTS >= R, "the counts below assume that a unit's fragments fit the ring");
+  static_assert(SLOTS >= R, "the counts below assume an activation unit among the copies of the last SLOTS fragments");
   static_assert(4 * R * MT * 1024 <= 4 * WAVE_LDS, "the final reduction reuses the rings");
   __shared__ __attribute__((aligned(1024))) uint8_t smem[4 * WAVE_LDS];
   const int lane = threadIdx.x & 63;

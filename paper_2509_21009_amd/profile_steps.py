@@ -7,7 +7,7 @@ sequences of a workload, prefills them, runs a fixed number of decode steps
 one device-to-device copy of a known size, whose counter readings calibrate
 the others.  Typical use, from the repository root:
 
-    rocprofv3 --pmc FETCH_SIZE --kernel-include-regex "k_gemm_deep|copy" \\
+    rocprofv3 --pmc FETCH_SIZE --kernel-include-regex "k_gemm_deep|k_gemm_ring|copy" \\
         -- python3 -u paper_2509_21009_amd/profile_steps.py --workload 7b-long --seqs 64 --steps 4
 
 All inputs are the seeded synthetic workloads of ``workloads``.

@@ -222,7 +222,7 @@ def test_tail_batched_rollout_rejects_null_engine(lib):
 
 def test_bench_reports_counter_traffic_only_for_the_measured_kernel(tmp_path):
     """roofline.traffic comes from a calibrated counter record and is dropped when the workload
-    or kernel differs or the deep kernel's source no longer matches the recorded hash."""
+    or kernel differs or the decode kernels' source no longer matches the recorded hash."""
     import json
     import bench
     from paper_2509_21009_amd.counter_traffic import HELPERS, PLANS, SOURCE, deep_source_digest

@@ -347,7 +347,7 @@ def test_packed_weights_give_identical_logits():
     """The decode GEMMs read a packed copy of the weights when the engine has one
     (rp_engine_set_packed_weights); every lane loads the same MFMA operand as from the
     row-major matrix, so prefill and teacher-forced decode logits must be bitwise equal with
-    and without it, over the deep kernel's regimes (1-4 activation tiles, K-split down and
+    and without it, over the decode kernels' regimes (1-4 activation tiles, K-split down and
     q/k/v projections, a ragged LM head of 8,320 rows) at the 7B layer shape."""
     R = rp()
     s = truncated(SHAPES["qwen2.5-7b"], 2, vocab=8320)
