@@ -21,7 +21,7 @@ projected length of a running request is the mean of the historical lengths
 above what it has already generated.
 
     python3 paper_2509_21009_amd/replica_sim.py --trace results/step_trace_7b.json
-    python3 paper_2509_21009_amd/replica_sim.py --model 3.5135,0.018858,5.9101e-6 --prefill-model 0,0.013172,0
+    python3 paper_2509_21009_amd/replica_sim.py --model 2.8765,0.012042,9.1498e-6 --prefill-model 0,0.011174,0
 """
 from __future__ import annotations
 
