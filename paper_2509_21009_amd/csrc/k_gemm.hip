@@ -237,7 +237,7 @@ __global__ __launch_bounds__(256) void k_gemm_deep(GemmArgs a, int units_per_spl
 // fragments x 4 activation tiles leave no registers for more), and gate/up of
 // the 7B took 62 us at 64 rows against 46 at 16.  Here weights and activations are copied
 // into LDS (buffer_load ... lds), 40 KB per wave: two units of activations and a
-// ring of the next 12-16 weight fragments, each refilled as soon as it is in
+// ring of the next 12-18 weight fragments, each refilled as soon as it is in
 // registers, so about 30 KB per wave stay in flight whatever the MFMAs do.  A wave
 // waits for its own copies by count (they complete in order) and reads a
 // fragment while the MFMAs of the one before run.  Copies past the wave's last
